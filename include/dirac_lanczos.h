@@ -481,7 +481,10 @@ const char *dirac_lanczos_hermite_last_error(void);
  *   (24 * compute units)) within 2..8, i.e. row chunks of at least 24 rows
  *   where the grid allows); the row chunks are re-planned for one resident
  *   round of waves.  *waves_out (HOST, may
- *   be NULL) receives the value in use (capped by occupancy).
+ *   be NULL) receives the value in use (capped by occupancy).  Grids of up to
+ *   about 1.1 million sites take their time steps in resident launches of up to
+ *   64 steps instead of sweeps (except with an adaptive dimension, in the
+ *   memory-saving variant and under stream capture), which this does not change.
  * dirac_lanczos_batch_set_launch: rows per chunk of the batched sweeps
  *   (>= 4; 0: the default choice, the smallest power of two giving at most
  *   one resident round of waves).  *rows_out (HOST, may be NULL) receives it.
@@ -492,7 +495,9 @@ dl_status dirac_lanczos_batch_set_launch(dl_batch *batch, int32_t rows_per_chunk
 
 /*
  * Kernel timing with HIP events recorded on the context's stream around every
- * launch of dirac_lanczos_step (a diagnostic for roofline measurements).
+ * launch of dirac_lanczos_step, or by the device's clock inside its resident
+ * launches (a diagnostic for roofline measurements; each iteration counts as a
+ * launch of its class).
  * Classes: 0 first Lanczos iteration; 1 recurrence sweeps whose operands are
  * all Krylov vectors (iterations >= 4, each reads u_{p-1}, u_{p-2} and writes
  * u_p); 2 recurrence sweeps that read psi (iterations 2 and 3); 3 tridiagonal

@@ -17,11 +17,16 @@
 namespace dlh {
 
 struct Layout {
+    // comm: exchange buffers of the resident steps, at the start of every
+    // workspace of a grid that takes them (their words must never be
+    // overwritten by anything else); chain, ticks: see dl::ResidentArgs
+    size_t comm = 0, chain = 0, ticks = 0;
+    size_t resident = 0;  // bytes of the three regions
     size_t sc = 0, alpha = 0, gamma = 0, partials = 0, fields = 0, stats = 0, vecs = 0, total = 0;
     int ab_len = 0;
 };
 
-inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+constexpr size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 inline size_t vec_elems(const dl_params &p) { return (size_t)2 * (size_t)p.nx * (size_t)p.ny; }
 // Byte stride between workspace vectors: padded so that vectors streamed
 // together are not a power of two apart.
@@ -135,6 +140,7 @@ struct dl_context {
     int combine_blocks = 1024;       // recombination (narrow form) and second-run accumulation
     bool combine_wide = false;       // recombination in the wide form (more sites per thread)
     int combine_blocks_wide = 1024;  // its workgroups
+    dl::ResidentTiles resident{};    // tiles of the resident steps (rows = 0: not used)
     int sweep_waves = 8;  // waves per compute unit of the sweeps (launch shape)
     std::vector<double> host_fields;
     std::vector<dl::StepStat> host_stats;
@@ -146,6 +152,20 @@ struct dl_context {
     size_t ev_used = 0;
     int64_t t_launches[5] = {0, 0, 0, 0, 0};
     double t_ms[5] = {0, 0, 0, 0, 0};
+    // resident steps count their ticks per class on the device (Layout::ticks);
+    // base: the counts when timing started
+    unsigned long long ticks_base[5] = {0, 0, 0, 0, 0};
+    hipError_t read_ticks(unsigned long long (&tk)[5])
+    {
+        hipError_t e = hipMemcpyAsync(tk, ws + L.ticks, sizeof(tk), hipMemcpyDeviceToHost, stream);
+        return e != hipSuccess ? e : hipStreamSynchronize(stream);
+    }
+    // the failure a non-zero Scalars::status stands for
+    dl_status status_fail(int status, const std::string &msg)
+    {
+        if (status == dl::kStatusTimeout) return fail(DL_ERR_DEVICE, "a resident step waited too long: " + msg);
+        return fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction " + msg);
+    }
     // asynchronous steps (stats == NULL): two pinned host buffers stage the
     // per-step fields of a chunk; an event after each upload guards the
     // buffer's reuse.  The statistics of the last chunk stay on the device
@@ -252,6 +272,22 @@ dl_status run_build(dl_context *ctx, const Engine &e, const dl::Op &op, const do
 // One whole step by the second Lanczos run (three rolling Krylov vectors).
 dl_status run_twice(dl_context *ctx, const Engine &e, const dl::Op &op, const double2 *in, double2 *out,
                     const double *field, dl::StepStat *stat, double *partials);
+// n steps (any number) from step `first` of a call in resident launches; *done
+// receives the steps enqueued, which are fewer than n when the path is not
+// available (the caller runs the others as sweeps).
+struct ResidentRun {
+    double2 *psi[2];
+    size_t state_stride = 0, basis_step = 0;
+    char *basis = nullptr;
+    size_t vstride = 0;
+    const double *fields = nullptr;
+    ptrdiff_t field_stride = 2;
+    dl::StepStat *stats = nullptr;
+    char *keep = nullptr;
+    size_t keep_step = 0, keep_alpha = 0, keep_gamma = 0;
+};
+dl_status run_resident(dl_context *ctx, const Engine &e, const dl::Op &op, const ResidentRun &r, int first, int n,
+                       int *done);
 // Where the recombination also copies the step's scalars, alpha and gamma
 // (dst == NULL: nowhere); see dl::CombArgs::keep.
 struct KeepDst {
@@ -271,6 +307,9 @@ void configure_launch(dl_context *ctx);
 // step call that dirac_lanczos_wait has not reported; DL_OK otherwise.  Every
 // synchronous entry point that resets the scalars calls it first.
 dl_status take_async_failure(dl_context *ctx);
+unsigned long long *ticks_of(const dl_context *ctx);
+// Scalars (and after a timeout the exchange buffers) back to a usable state.
+void clear_failure(dl_context *ctx, int status);
 
 // Eigen mode with full reorthogonalisation (eigen.cpp); vecs (device, may be
 // NULL) receives the Ritz vectors of the reported values.

@@ -37,7 +37,12 @@ struct Scalars {
     // (0: m), and the small exponential predicts knext for the next step
     int kmin, kmax, knext;
     double ktol;                   // per-step bound on the error estimate (0: off)
+    unsigned int epoch;            // last epoch of the resident steps' exchange (never reset within a workspace)
+    unsigned int pad;
 };
+// Scalars::status of a call whose resident step waited too long (0 ok, 3 a
+// non-finite reduction).
+constexpr int kStatusTimeout = 4;
 
 struct StepStat {
     double err_est;
@@ -134,6 +139,73 @@ struct CombArgs {
     size_t keep_alpha, keep_gamma;
     int keep_nab;
 };
+
+// ---------------------------------------------------------------------------
+// Resident time steps (resident_kernels.hip): the grid cut into ntx x nty tiles,
+// one workgroup each, tile (i, j) covering columns x0(i) .. x0(i + 1) - 1 and
+// rows y0(j) .. y0(j + 1) - 1, at most tx x ty sites; a thread owns `rows` rows
+// of one column of the tile and its one-site rim.  rows = 0: the grid does not
+// take this path.
+// ---------------------------------------------------------------------------
+constexpr int kResidentThreads = 512;
+constexpr int kResidentWgs = 256;    // most workgroups (one per compute unit)
+constexpr int kResidentSlots = 300;  // most published sites per tile
+constexpr int kResidentSteps = 64;   // steps per launch
+constexpr int kChainLen = 1 + 2 * kMaxM;  // k_eff, alpha_1.., gamma_1.. of a step
+// exchange buffers: two epochs of the partial sums (ten words per workgroup
+// and per copy of a group's sums) and of the published sites (eight words each)
+constexpr size_t kCommRed = sizeof(unsigned long long) * 2 * 10 * (kResidentWgs + 128);
+constexpr size_t kCommBytes = kCommRed + sizeof(unsigned long long) * 2 * 8 * (size_t)kResidentSlots * kResidentWgs;
+// Whether a run of `rows` rows per thread goes with two tile buffers in LDS.
+constexpr bool resident_two_buffers(int rows) { return rows <= 4; }
+struct ResidentTiles {
+    int ntx = 0, nty = 0, tx = 0, ty = 0, rows = 0;
+    __host__ __device__ int x0(int i, int nx) const { return (int)((long long)i * nx / ntx); }
+    __host__ __device__ int y0(int j, int ny) const { return (int)((long long)j * ny / nty); }
+    __host__ __device__ int slots() const { return 2 * tx + 2 * ty + 4; }
+    // the tile with a two-site rim (a spare site per plane, two planes per
+    // buffer), at least the scratch of the small exponential
+    size_t lds_bytes() const
+    {
+        const size_t tile = sizeof(double2) * (resident_two_buffers(rows) ? 4 : 2) *
+                            ((size_t)(tx + 4) * (size_t)(ty + 4) + 1);
+        const size_t scratch = sizeof(double) * 64 * (kMaxM + 1);
+        return tile > scratch ? tile : scratch;
+    }
+};
+struct ResidentArgs {
+    Op op;
+    ResidentTiles t;
+    int m, n_steps;
+    double2 *psi[2];           // step s reads psi[s & 1] and writes psi[(s + 1) & 1], or,
+    size_t state_stride;       // when not 0, reads and writes states s and s + 1 of that byte stride from psi[0]
+    char *basis;               // u_2 .. u_m of a step (vstride apart), steps basis_step apart
+    size_t vstride, basis_step;
+    int stream_basis;          // 1: the basis of a step exceeds the last-level cache
+    const double *fields;      // (gx_hom, gy_hom) of step s at fields + s field_stride
+    ptrdiff_t field_stride;
+    Scalars *sc;
+    StepStat *stats;
+    double *chain;             // kChainLen doubles per step, or NULL
+    char *keep;                // per step (keep_step apart): Scalars, alpha and gamma for the adjoint, or NULL
+    size_t keep_step, keep_alpha, keep_gamma;
+    unsigned long long *red, *halo;  // exchange buffers
+    unsigned long long *ticks;       // per kernel class, the launch's 100 MHz ticks are added (timing), or NULL
+    __host__ __device__ double2 *state_in(int s) const
+    {
+        if (state_stride) return reinterpret_cast<double2 *>(reinterpret_cast<char *>(psi[0]) + (size_t)s * state_stride);
+        return psi[s & 1];
+    }
+    __host__ __device__ double2 *state_out(int s) const { return state_in(s + 1); }
+};
+// Tiles of a grid for at most `wgs` workgroups (rows = 0 when it does not fit).
+ResidentTiles resident_tiles(int nx, int ny, int wgs);
+// Cooperative launch of n_steps <= kResidentSteps steps (any error: nothing ran).
+hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st);
+void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *stats, int first, int n, double reps,
+                            double rabs, hipStream_t st);
+// Exchange buffers, epoch and ticks to zero (a new workspace, or after a timeout).
+void launch_zero_comm(void *comm, Scalars *sc, unsigned long long *ticks, hipStream_t st);
 
 // One term of the recombination during a second Lanczos run (the basis is not
 // stored): out = c_1 psi for p = 1, out += c_p u_p for p = 2..k_eff; the

@@ -30,8 +30,17 @@ Layout plan(const dl_params &p, int mode, int k_eigen)
     const bool eig = mode == DL_MODE_EIGEN || mode == DL_MODE_EIGEN_REORTH;
     L.ab_len = std::max(m, eig ? k_eigen + 1 : 0) + 3;
     size_t off = 0;
+    if (dl::resident_tiles(p.nx, p.ny, dl::kResidentWgs).rows > 0) {
+        L.comm = off;
+        off = align256(off + dl::kCommBytes);
+    }
     L.sc = off;
     off = align256(off + sizeof(dl::Scalars));
+    L.chain = off;
+    off = align256(off + sizeof(double) * dl::kChainLen * dl::kResidentSteps);
+    L.ticks = off;
+    off = align256(off + sizeof(unsigned long long) * 5);
+    L.resident = off - align256(sizeof(dl::Scalars));
     L.alpha = off;
     off = align256(off + sizeof(double) * L.ab_len);
     L.gamma = off;
@@ -326,8 +335,84 @@ dl_status run_finish(dl_context *ctx, const Engine &e, const double2 *in, double
     return DL_OK;
 }
 
+constexpr size_t kLastLevelCache = size_t(256) << 20;  // bytes shared by the chip's dies
+
+dl_status run_resident(dl_context *ctx, const Engine &e, const dl::Op &op, const ResidentRun &r, int first, int n,
+                       int *done)
+{
+    *done = 0;
+    if (ctx->resident.rows == 0) return DL_OK;
+    hipStream_t st = ctx->stream;
+    // a cooperative launch is not recorded into a graph; a captured call runs
+    // as sweeps
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return DL_OK;
+    }
+    if (cap != hipStreamCaptureStatusNone) return DL_OK;
+    char *ws = ctx->ws;
+    const Layout &L = ctx->L;
+    double reps, rabs;
+    store_rounding(ctx->p, reps, rabs);
+    dl::ResidentArgs a{};
+    a.op = op;
+    a.t = ctx->resident;
+    a.m = e.m;
+    a.state_stride = r.state_stride;
+    a.vstride = r.vstride;
+    a.basis_step = r.basis_step;
+    a.stream_basis = (size_t)(e.m - 1) * r.vstride > kLastLevelCache;
+    a.field_stride = r.field_stride;
+    a.sc = e.sc;
+    a.chain = e.mixed ? reinterpret_cast<double *>(ws + L.chain) : nullptr;
+    a.keep_step = r.keep_step;
+    a.keep_alpha = r.keep_alpha;
+    a.keep_gamma = r.keep_gamma;
+    a.red = reinterpret_cast<unsigned long long *>(ws + L.comm);
+    a.halo = reinterpret_cast<unsigned long long *>(ws + L.comm + dl::kCommRed);
+    a.ticks = ctx->timing ? ticks_of(ctx) : nullptr;
+    for (int i = 0; i < n; i += dl::kResidentSteps) {
+        a.n_steps = std::min(dl::kResidentSteps, n - i);
+        a.psi[0] = r.psi[i & 1];
+        a.psi[1] = r.psi[(i + 1) & 1];
+        if (r.state_stride)
+            a.psi[0] = reinterpret_cast<double2 *>(reinterpret_cast<char *>(r.psi[0]) + (size_t)i * r.state_stride);
+        a.basis = r.basis + (size_t)i * r.basis_step;
+        a.fields = r.fields + (ptrdiff_t)i * r.field_stride;
+        a.stats = r.stats + i;
+        a.keep = r.keep ? r.keep + (size_t)i * r.keep_step : nullptr;
+        if (dl::launch_resident(a, e.mixed, st) != hipSuccess) {
+            // not available on this device or in its present partition: the
+            // context uses sweeps from here on
+            (void)hipGetLastError();
+            ctx->resident = dl::ResidentTiles{};
+            return DL_OK;
+        }
+        *done = i + a.n_steps;
+        if (e.mixed) dl::launch_resident_bounds(a.chain, e.sc, a.stats, first + i, a.n_steps, reps, rabs, st);
+        if (ctx->timing) {  // the times are read by dirac_lanczos_timing
+            const int per[5] = {1, std::max(e.m - 3, 0), std::min(e.m, 3) - 1, 1, 1};
+            for (int c = 0; c < 5; ++c) ctx->t_launches[c] += (int64_t)a.n_steps * per[c];
+        }
+    }
+    return DL_OK;
+}
+
 // A failure of an earlier asynchronous call that dirac_lanczos_wait has not
 // reported yet: synchronise, read the scalars, and report and clear it.
+unsigned long long *ticks_of(const dl_context *ctx)
+{
+    return reinterpret_cast<unsigned long long *>(ctx->ws + ctx->L.ticks);
+}
+
+void clear_failure(dl_context *ctx, int status)
+{
+    // after a timeout the workgroups may have left at different epochs
+    if (status == dl::kStatusTimeout) dl::launch_zero_comm(ctx->ws + ctx->L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
+    dl::launch_reset(ctx->sc(), ctx->stream);
+}
+
 dl_status take_async_failure(dl_context *ctx)
 {
     if (!ctx->async_pending) return DL_OK;
@@ -336,10 +421,9 @@ dl_status take_async_failure(dl_context *ctx)
     dl::Scalars hs;
     DL_HIP(ctx, hipMemcpy(&hs, ctx->sc(), sizeof(hs), hipMemcpyDeviceToHost));
     if (hs.status == 0) return DL_OK;
-    dl::launch_reset(ctx->sc(), ctx->stream);
+    clear_failure(ctx, hs.status);
     DL_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    return ctx->fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction in an asynchronous call after " +
-                                           std::to_string(hs.steps_done) + " of its steps");
+    return ctx->status_fail(hs.status, "in an asynchronous call after " + std::to_string(hs.steps_done) + " of its steps");
 }
 
 }  // namespace dlh
@@ -404,6 +488,9 @@ void set_tiles(dl_context *ctx, int cap)
     ctx->combine_blocks = dl::combine_grid(vec_elems(p) / 2, mixed, ctx->cus, !mixed);
     ctx->combine_wide = dl::combine_wide(vec_elems(p) / 2, mixed, ctx->cus);
     ctx->combine_blocks_wide = dl::combine_grid(vec_elems(p) / 2, mixed, ctx->cus, ctx->combine_wide);
+    // (the workspace holds the exchange buffers when the grid fits kResidentWgs)
+    ctx->resident = dl::resident_tiles(p.nx, p.ny, dl::kResidentWgs);
+    if (ctx->resident.ntx * ctx->resident.nty > ctx->cus) ctx->resident = dl::ResidentTiles{};
 }
 
 }  // namespace
@@ -473,6 +560,7 @@ dl_status dirac_lanczos_init(const dl_params *params, void *workspace, size_t ws
     ctx->L = L;
     ctx->cus = prop.multiProcessorCount;
     set_tiles(ctx, 0);
+    if (ctx->resident.rows > 0) dl::launch_zero_comm(ctx->ws + L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
     dl::launch_reset(ctx->sc(), ctx->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -586,14 +674,26 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
                           st);
     DL_HIP(ctx, hipGetLastError());
     double cum = 0.0;
-    int completed = 0;
+    int completed = 0, status = 0;
     bool aborted = false;
     ctx->host_stats.resize(kChunk);
     for (int s0 = 0; s0 < n_steps && !aborted; s0 += kChunk) {
         const int nc = std::min(kChunk, n_steps - s0);
         const dl_status sf = stage_fields(ctx, async, t0, dt, s0, nc, fields);
         if (sf != DL_OK) return sf;
-        for (int i = 0; i < nc; ++i) {
+        int first = 0;
+        if (!lowmem && !(ktol > 0.0)) {
+            ResidentRun r;
+            r.psi[0] = (s0 % 2 == 0) ? psi : state;
+            r.psi[1] = (s0 % 2 == 0) ? state : psi;
+            r.basis = eng.basis;
+            r.vstride = vstride;
+            r.fields = fields;
+            r.stats = dstats;
+            const dl_status sr = run_resident(ctx, eng, op, r, s0, nc, &first);
+            if (sr != DL_OK) return sr;
+        }
+        for (int i = first; i < nc; ++i) {
             const int g = s0 + i;
             double2 *in = (g % 2 == 0) ? psi : state;
             double2 *out = (g % 2 == 0) ? state : psi;
@@ -633,7 +733,8 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
             }
         }
         completed = hs.steps_done;
-        if (hs.status != 0) aborted = true;
+        status = hs.status;
+        if (status != 0) aborted = true;
     }
     if (async) {
         // the state after the completed steps is copied to psi on the device
@@ -652,9 +753,10 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
         DL_HIP(ctx, hipMemcpyAsync(psi, state, n * 16, hipMemcpyDeviceToDevice, st));
         DL_HIP(ctx, hipStreamSynchronize(st));
     }
-    if (aborted)
-        return ctx->fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction after " +
-                                               std::to_string(completed) + " completed steps");
+    if (aborted) {
+        if (status == dl::kStatusTimeout) clear_failure(ctx, status);
+        return ctx->status_fail(status, "after " + std::to_string(completed) + " completed steps");
+    }
     return DL_OK;
 }
 
@@ -830,10 +932,9 @@ dl_status dirac_lanczos_wait(dl_context *ctx, dl_step_stat *stats, int32_t n_sta
     }
     ctx->async_pending = false;
     if (hs.status != 0) {
-        dl::launch_reset(ctx->sc(), ctx->stream);
+        clear_failure(ctx, hs.status);
         DL_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        return ctx->fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction after " + std::to_string(hs.steps_done) +
-                                               " completed steps of the last call");
+        return ctx->status_fail(hs.status, "after " + std::to_string(hs.steps_done) + " completed steps of the last call");
     }
     return DL_OK;
 }
@@ -852,10 +953,12 @@ dl_status dirac_lanczos_timing(dl_context *ctx, int32_t enable, dl_timing *out)
 {
     if (!ctx) return DL_ERR_INVALID;
     DL_HIP(ctx, ctx->harvest());
+    unsigned long long tk[5] = {0, 0, 0, 0, 0};
+    if (ctx->resident.rows > 0 && (ctx->timing || enable)) DL_HIP(ctx, ctx->read_ticks(tk));
     if (out) {
         for (int i = 0; i < 5; ++i) {
             out->launches[i] = ctx->t_launches[i];
-            out->total_ms[i] = ctx->t_ms[i];
+            out->total_ms[i] = ctx->t_ms[i] + (ctx->timing ? 1e-5 * (double)(tk[i] - ctx->ticks_base[i]) : 0.0);
         }
     }
     if (enable) {
@@ -873,6 +976,7 @@ dl_status dirac_lanczos_timing(dl_context *ctx, int32_t enable, dl_timing *out)
         for (int i = 0; i < 5; ++i) {
             ctx->t_launches[i] = 0;
             ctx->t_ms[i] = 0.0;
+            ctx->ticks_base[i] = tk[i];
         }
         ctx->timing = true;
     } else {

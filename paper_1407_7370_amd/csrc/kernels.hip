@@ -69,6 +69,41 @@ Tiles make_tiles(int nx, int ny, int halo, int target_waves)
     return t;
 }
 
+ResidentTiles resident_tiles(int nx, int ny, int wgs)
+{
+    // the fewest rows per thread first (the arithmetic of an iteration), then
+    // the shortest border; a workgroup per kMinSites sites at most (fewer
+    // workgroups fold and wait for fewer partials)
+    constexpr int kRows[] = {1, 2, 3, 4, 6, 8, 10};
+    constexpr size_t kMaxLds = 152 * 1024;
+    constexpr long kMinSites = 256;
+    ResidentTiles best;
+    long best_cost = 0;
+    const long sites = (long)nx * ny;
+    const int want = (int)std::max(1L, std::min((long)wgs, sites / kMinSites));
+    for (int ntx = 1; ntx <= want && (ntx == 1 || nx / ntx >= 4); ++ntx) {
+        ResidentTiles t;
+        t.ntx = ntx;
+        t.tx = (nx + ntx - 1) / ntx;
+        const int most = std::max(1, std::min(want / ntx, ny / 4));
+        t.ty = (ny + most - 1) / most;
+        t.nty = (ny + t.ty - 1) / t.ty;
+        const int cols = t.tx + 2;
+        for (int k : kRows) {
+            t.rows = k;
+            if (cols * ((t.ty + 2 + k - 1) / k) <= kResidentThreads && t.lds_bytes() <= kMaxLds) break;
+            t.rows = 0;
+        }
+        if (t.rows == 0 || t.slots() > kResidentSlots) continue;
+        const long cost = 4096L * t.rows + t.slots();
+        if (best.rows == 0 || cost < best_cost) {
+            best = t;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 void launch_first(const Op &op, const Tiles &t, const double2 *psi, const double *field,
                   double *alpha, double *gamma, Scalars *sc, double *partials, int m, int shift,
                   hipStream_t st)

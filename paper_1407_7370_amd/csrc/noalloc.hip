@@ -20,7 +20,15 @@ using namespace dlh;
 
 namespace {
 
-constexpr size_t kScratchBytes = size_t(64) << 20;
+// The scratch starts with the exchange buffers of the resident steps (zero when
+// the program starts; a grid that does not take that path begins behind them,
+// where the scalars with the epoch are in every layout), then 64 MiB for the
+// rest of the workspace and the resident steps' small arrays.
+constexpr size_t kProblemBytes = size_t(64) << 20;
+constexpr size_t kExchange = align256(dl::kCommBytes);
+constexpr size_t kScratchBytes = kExchange + kProblemBytes + (size_t(128) << 10);
+static_assert(align256(sizeof(double) * dl::kChainLen * dl::kResidentSteps) + 256 <= (size_t(128) << 10),
+              "the scratch holds the resident steps' arrays");
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 // Per-device address of `scratch` (the array's name is a host-side stand-in,
@@ -52,7 +60,7 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     if (!psi_v || n_steps < 0 || !(dt != 0.0) || !std::isfinite(dt) || !std::isfinite(t0)) return DL_ERR_INVALID;
     if (params->pulse_kind == DL_PULSE_FOURIER_SIN2 && !params->coef) return DL_ERR_INVALID;
     const Layout L = plan(*params, DL_MODE_STEP, 0);
-    if (L.total > kScratchBytes) return DL_ERR_WORKSPACE;  // beyond the static scratch
+    if (L.total - L.resident > kProblemBytes) return DL_ERR_WORKSPACE;  // beyond the static scratch
     if (n_steps == 0) return DL_OK;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return DL_ERR_DEVICE;
@@ -81,8 +89,9 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     dl_context ctx;
     ctx.p = p;
     ctx.stream = st;
-    ctx.ws = static_cast<char *>(ws);
-    ctx.ws_bytes = kScratchBytes;
+    const size_t skip = L.sc == 0 ? kExchange : 0;  // no exchange buffers in this layout
+    ctx.ws = static_cast<char *>(ws) + skip;
+    ctx.ws_bytes = kScratchBytes - skip;
     ctx.L = L;
     ctx.cus = cus;
     configure_launch(&ctx);
@@ -104,7 +113,7 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     dl::launch_reset(sc, st);
     if (hipGetLastError() != hipSuccess) return DL_ERR_DEVICE;
     double cum = 0.0;
-    int completed = 0;
+    int completed = 0, status = 0;
     bool aborted = false;
     for (int s0 = 0; s0 < n_steps && !aborted; s0 += kRound) {
         const int nc = std::min(kRound, n_steps - s0);
@@ -116,7 +125,16 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
             fb.f[2 * i + 1] = kf * chir(p) * a[1];
         }
         hipLaunchKernelGGL(k_put_fields, dim3(1), dim3(2 * kRound), 0, st, fields, fb, nc);
-        for (int i = 0; i < nc; ++i) {
+        int first = 0;
+        ResidentRun r;
+        r.psi[0] = (s0 % 2 == 0) ? psi : state;
+        r.psi[1] = (s0 % 2 == 0) ? state : psi;
+        r.basis = eng.basis;
+        r.vstride = eng.vstride;
+        r.fields = fields;
+        r.stats = dstats;
+        if (run_resident(&ctx, eng, op, r, s0, nc, &first) != DL_OK) return DL_ERR_DEVICE;
+        for (int i = first; i < nc; ++i) {
             const int g = s0 + i;
             double2 *in = (g % 2 == 0) ? psi : state;
             double2 *out = (g % 2 == 0) ? state : psi;
@@ -147,7 +165,8 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
             }
         }
         completed = hsc.steps_done;
-        aborted = hsc.status != 0;
+        status = hsc.status;
+        aborted = status != 0;
     }
     if (stats && aborted)
         for (int i = completed; i < n_steps; ++i) {
@@ -158,5 +177,9 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     dl::launch_finish_copy(sc, state, psi, n, cus, st);
     if (hipGetLastError() != hipSuccess) return DL_ERR_DEVICE;
     if (stats && hipStreamSynchronize(st) != hipSuccess) return DL_ERR_DEVICE;
+    if (aborted && status == dl::kStatusTimeout) {
+        clear_failure(&ctx, status);
+        return DL_ERR_DEVICE;
+    }
     return aborted ? DL_ERR_NONFINITE : DL_OK;
 }

@@ -898,6 +898,14 @@ __global__ __launch_bounds__(kBlock) void k_recur(PassArgs a)
 // ---------------------------------------------------------------------------
 constexpr int kChebMaxTerms = 224;
 
+// Orders this wave's LDS accesses (the functions below run in one wave, alone
+// in its workgroup or beside others: no workgroup barrier).
+__device__ __forceinline__ void wave_sync()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __device__ __forceinline__ double wave_max(double v)
 {
 #pragma unroll
@@ -998,7 +1006,7 @@ __device__ bool cheb_exp_e1(double d, double e, double em, int kd, int lane, dou
     const double c0 = 0.5 * (glo + ghi), R = 0.5 * (ghi - glo);
     const int N = R > 0.0 ? (R < 1e4 ? cheb_terms(R) : kChebMaxTerms + 1) : 0;
     if (N > kChebMaxTerms) return false;
-    __syncthreads();  // jb of a previous call is read up to here
+    wave_sync();  // jb of a previous call is read up to here
     if (lane == 0) {
         double s = 1.0;
         if (N > 0) {
@@ -1012,7 +1020,7 @@ __device__ bool cheb_exp_e1(double d, double e, double em, int kd, int lane, dou
         }
         jscale = s;
     }
-    __syncthreads();
+    wave_sync();
     // X = (T' - c0 I) / R on this lane's row (zero rows beyond kd)
     const double ir = N > 0 ? 1.0 / R : 0.0;
     const double xd = lane < kd ? (d - c0) * ir : 0.0, xe = e * ir, xem = em * ir;
@@ -1190,7 +1198,7 @@ __device__ double storage_bound(double d, double e, double em, int k, int lane, 
         const int N = R > 0.0 ? min((int)ceil(R + 6.0 * cbrt(R) + 12.0), kBoundMaxTerms) : 0;
         double *vt = lds;                // row n: T_n(X) e_1 (n <= N + 3)
         double *jt = lds + kBoundVecRows * 64;  // row q: J_n(t_q R), unnormalised
-        __syncthreads();  // LDS of an earlier use is read up to here
+        wave_sync();  // LDS of an earlier use is read up to here
         if (lane < nb) {
             double *row = jt + lane * kBoundRow;
             double s = 0.0, wq = 0.0;
@@ -1226,7 +1234,7 @@ __device__ double storage_bound(double d, double e, double em, int k, int lane, 
             tm = tc;
             tc = tn;
         }
-        __syncthreads();
+        wave_sync();
         // per node, halved: a = J_0 v_0 / 2 - J_2 v_2 + J_4 v_4 - ..., b = -J_1 v_1
         // + J_3 v_3 - ..., so that s_j(t_q) = 2 (a + i b) times the
         // normalisation of the node's Bessel values.  The vector needs kk
@@ -1301,6 +1309,93 @@ __device__ double storage_bound(double d, double e, double em, int k, int lane, 
     return g1 * v;
 }
 
+// This lane's component of exp(-iT') e_1 for the k x k tridiagonal T' (as
+// cheb_exp_e1, any spectrum) by the eigendecomposition.  zpr: (kMaxM + 1) * 64
+// doubles of LDS, wre, wim: kMaxM each.  Called by one whole wave.
+__device__ __forceinline__ void qr_exp_e1(double d, double e, int k, int lane, double *zpr, double *wre, double *wim,
+                                          double &cr, double &ci)
+{
+    cr = ci = 0.0;
+#define ZZ(i) zpr[(i) * 64 + lane]
+    for (int i = 0; i < k; ++i) ZZ(i) = (i == lane) ? 1.0 : 0.0;
+    const double eps = 2.220446049250313e-16;
+    for (int iter = 0; iter < 40 * kMaxM; ++iter) {
+        // negligible couplings are set to zero; find the last unreduced block [l, h]
+        const double dn = __shfl_down(d, 1, 64);
+        const bool live = lane + 1 < k && e != 0.0;
+        const bool tiny = live && fabs(e) <= eps * (fabs(d) + fabs(dn));
+        if (tiny) e = 0.0;
+        const unsigned long long mask = __ballot(live && !tiny);
+        if (mask == 0ull) break;
+        const int hb = 63 - __clzll(mask);  // highest coupling still live
+        const unsigned long long below = ~mask & ((1ull << hb) - 1ull);
+        const int l = below ? 64 - __clzll(below) : 0;
+        const int h = hb + 1;
+        // Wilkinson shift from the trailing 2x2 block of [l, h]
+        const double dh1 = __shfl(d, h - 1, 64), dh = __shfl(d, h, 64), eh1 = __shfl(e, h - 1, 64);
+        const double delta = 0.5 * (dh1 - dh);
+        const double b2 = eh1 * eh1;
+        const double mu = dh - b2 / (delta + copysign(sqrt(delta * delta + b2), delta));
+        double aq = __shfl(d, l, 64);  // current d_q
+        double bq = __shfl(e, l, 64);  // current e_q
+        double x = aq - mu, z = bq;
+        double aq1n = __shfl(d, l + 1, 64);
+        double bq1n = (l + 1 < h) ? __shfl(e, l + 1, 64) : 0.0;
+        double zq = ZZ(l);
+        for (int q = l; q < h; ++q) {
+            const double aq1 = aq1n, bq1 = bq1n;
+            // entries of the next step, fetched ahead (lanes > q+1 are untouched so far)
+            aq1n = __shfl(d, min(q + 2, 63), 64);
+            bq1n = (q + 2 < h) ? __shfl(e, min(q + 2, 63), 64) : 0.0;
+            const double zq1 = ZZ(q + 1);
+            const double rr = x * x + z * z;
+            double c = 1.0, s = 0.0, r = 0.0;
+            if (rr > 0.0) {
+                const double ir = rsqrt(rr);
+                c = x * ir;
+                s = -z * ir;
+                r = rr * ir;
+            }
+            if (q > l && lane == q - 1) e = r;
+            const double cc = c * c, ss = s * s, cs = c * s;
+            const double dq = cc * aq - 2.0 * cs * bq + ss * aq1;
+            const double dq1 = ss * aq + 2.0 * cs * bq + cc * aq1;
+            const double eq = cs * (aq - aq1) + (cc - ss) * bq;
+            if (lane == q) d = dq;
+            ZZ(q) = c * zq - s * zq1;
+            zq = s * zq + c * zq1;
+            aq = dq1;
+            if (q + 1 < h) {
+                x = eq;
+                z = -s * bq1;
+                bq = c * bq1;
+            } else {
+                if (lane == q) e = eq;
+                if (lane == q + 1) d = dq1;
+            }
+        }
+        ZZ(h) = zq;
+    }
+    // c_j = sum_i Z[j][i] exp(-i lambda_i) Z[0][i]; lambda_i is lane i's d
+    wave_sync();
+    if (lane < k) {
+        double sn, cs;
+        sincos(d, &sn, &cs);
+        const double z0 = zpr[lane * 64 + 0];
+        wre[lane] = z0 * cs;
+        wim[lane] = -z0 * sn;
+    }
+    wave_sync();
+    if (lane < k) {
+        for (int i = 0; i < k; ++i) {
+            const double zji = ZZ(i);
+            cr += zji * wre[i];
+            ci += zji * wim[i];
+        }
+    }
+#undef ZZ
+}
+
 __device__ __forceinline__ void tridiag_body(const double *alpha, const double *gamma, Scalars *sc, StepStat *stat,
                                              double reps, double rabs)
 {
@@ -1330,86 +1425,7 @@ __device__ __forceinline__ void tridiag_body(const double *alpha, const double *
     if (lane == 0) em = 0.0;
     const double rb = storage_bound(d, e, em, k, lane, g1, reps, rabs, zpr);
     double cr = 0.0, ci = 0.0;
-    if (!cheb_exp_e1(d, e, em, k, lane, cr, ci)) {
-#define ZZ(i) zpr[(i) * 64 + lane]
-        for (int i = 0; i < k; ++i) ZZ(i) = (i == lane) ? 1.0 : 0.0;
-        const double eps = 2.220446049250313e-16;
-        for (int iter = 0; iter < 40 * kMaxM; ++iter) {
-            // negligible couplings are set to zero; find the last unreduced block [l, h]
-            const double dn = __shfl_down(d, 1, 64);
-            const bool live = lane + 1 < k && e != 0.0;
-            const bool tiny = live && fabs(e) <= eps * (fabs(d) + fabs(dn));
-            if (tiny) e = 0.0;
-            const unsigned long long mask = __ballot(live && !tiny);
-            if (mask == 0ull) break;
-            const int hb = 63 - __clzll(mask);  // highest coupling still live
-            const unsigned long long below = ~mask & ((1ull << hb) - 1ull);
-            const int l = below ? 64 - __clzll(below) : 0;
-            const int h = hb + 1;
-            // Wilkinson shift from the trailing 2x2 block of [l, h]
-            const double dh1 = __shfl(d, h - 1, 64), dh = __shfl(d, h, 64), eh1 = __shfl(e, h - 1, 64);
-            const double delta = 0.5 * (dh1 - dh);
-            const double b2 = eh1 * eh1;
-            const double mu = dh - b2 / (delta + copysign(sqrt(delta * delta + b2), delta));
-            double aq = __shfl(d, l, 64);  // current d_q
-            double bq = __shfl(e, l, 64);  // current e_q
-            double x = aq - mu, z = bq;
-            double aq1n = __shfl(d, l + 1, 64);
-            double bq1n = (l + 1 < h) ? __shfl(e, l + 1, 64) : 0.0;
-            double zq = ZZ(l);
-            for (int q = l; q < h; ++q) {
-                const double aq1 = aq1n, bq1 = bq1n;
-                // entries of the next step, fetched ahead (lanes > q+1 are untouched so far)
-                aq1n = __shfl(d, min(q + 2, 63), 64);
-                bq1n = (q + 2 < h) ? __shfl(e, min(q + 2, 63), 64) : 0.0;
-                const double zq1 = ZZ(q + 1);
-                const double rr = x * x + z * z;
-                double c = 1.0, s = 0.0, r = 0.0;
-                if (rr > 0.0) {
-                    const double ir = rsqrt(rr);
-                    c = x * ir;
-                    s = -z * ir;
-                    r = rr * ir;
-                }
-                if (q > l && lane == q - 1) e = r;
-                const double cc = c * c, ss = s * s, cs = c * s;
-                const double dq = cc * aq - 2.0 * cs * bq + ss * aq1;
-                const double dq1 = ss * aq + 2.0 * cs * bq + cc * aq1;
-                const double eq = cs * (aq - aq1) + (cc - ss) * bq;
-                if (lane == q) d = dq;
-                ZZ(q) = c * zq - s * zq1;
-                zq = s * zq + c * zq1;
-                aq = dq1;
-                if (q + 1 < h) {
-                    x = eq;
-                    z = -s * bq1;
-                    bq = c * bq1;
-                } else {
-                    if (lane == q) e = eq;
-                    if (lane == q + 1) d = dq1;
-                }
-            }
-            ZZ(h) = zq;
-        }
-        // c_j = sum_i Z[j][i] exp(-i lambda_i) Z[0][i]; lambda_i is lane i's d
-        __syncthreads();
-        if (lane < k) {
-            double sn, cs;
-            sincos(d, &sn, &cs);
-            const double z0 = zpr[lane * 64 + 0];
-            wre[lane] = z0 * cs;
-            wim[lane] = -z0 * sn;
-        }
-        __syncthreads();
-        if (lane < k) {
-            for (int i = 0; i < k; ++i) {
-                const double zji = ZZ(i);
-                cr += zji * wre[i];
-                ci += zji * wim[i];
-            }
-        }
-#undef ZZ
-    }
+    if (!cheb_exp_e1(d, e, em, k, lane, cr, ci)) qr_exp_e1(d, e, k, lane, zpr, wre, wim, cr, ci);
     double ck = 0.0;
     if (lane < k) {
         // exp(-iT) = exp(-i sigma) exp(-iT') for the shifted tridiagonal T'

@@ -1,0 +1,142 @@
+"""The resident time steps (one launch for many steps of a grid that fits the
+chip's LDS) where they can go wrong: the smallest grids, tiles of unequal size,
+every number of rows per thread, both tile buffer schemes, periodic images that
+are the tile itself, more steps than one launch takes, several contexts and
+streams at once."""
+import numpy as np
+import pytest
+
+import harness as hz
+from paper_1407_7370_amd import packets
+
+pytestmark = pytest.mark.gpu
+
+C = 137.036
+EPS = 2.0 ** -52
+
+
+def say(msg):
+    print(f"[gpu case] {msg}", flush=True)
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    return oracle
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch
+
+
+def box(nx, ny, bcx, bcy, h=0.1, **kw):
+    p = dict(nx=nx, ny=ny, x_min=-0.5 * nx * h, x_max=0.5 * nx * h, y_min=-0.5 * ny * h, y_max=0.5 * ny * h, bc_x=bcx,
+             bc_y=bcy, mass=1.0, c=C, charge=-1.0, bz=0.0, pot_kind=0, pot_z=0.0, pot_a=0.0, pulse_kind=0,
+             pulse_e=(0.0, 0.0), a0=0.0, omega=0.0, t_pulse=1.0, coef=None)
+    p.update(kw)
+    return p
+
+
+FIELDS = dict(bz=0.6, pot_kind=1, pot_z=1.0, pot_a=1.0)
+
+
+# one tile (also its own periodic neighbour), tiles of four sites, unequal tiles
+@pytest.mark.parametrize("nx,ny,bcx,bcy", [(3, 3, 1, 1), (3, 4, 0, 1), (16, 5, 1, 0), (33, 17, 0, 0), (131, 77, 1, 1),
+                                           (9, 400, 0, 1), (290, 201, 1, 0)])
+@pytest.mark.parametrize("fields", [False, True])
+def test_small_grids_vs_oracle(torch_cuda, orc, nx, ny, bcx, bcy, fields):
+    """66 steps (a launch takes 64) with a laser pulse, m = 6."""
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    prob = box(nx, ny, bcx, bcy, pulse_kind=1, pulse_e=(0.6, 0.8), a0=30.0, omega=1.0, t_pulse=0.02,
+               **(FIELDS if fields else {}))
+    psi0 = packets.random_spinor(prob, nx) * 1e-2 + packets.gaussian_packet(prob, 1.0, (1.0, -2.0))
+    n, dt, m = 66, 1e-4, 6
+    say(f"resident {nx}x{ny} bc {bcx}{bcy} fields={fields}")
+    prop = Propagator(prob, m, "fp64")
+    psi = torch.from_numpy(psi0).cuda()
+    st = prop.step(psi, 0.0, dt, n)
+    prop.close()
+    ref, rst = orc.propagate(prob, psi0, 0.0, dt, n, m)
+    assert np.array_equal(st["k_eff"], rst["k_eff"])
+    # rounding of the step phase |dt H| per step, 64 roundings of it allowed
+    phase = dt * (C * C + 2 * C / 0.1 + 10 * C)
+    assert hz.rel_l2(psi.cpu().numpy(), ref) <= 64 * n * phase * EPS
+    np.testing.assert_allclose(st["norm2"], rst["norm2"], rtol=64 * n * EPS)
+
+
+# rows per thread 2, 3, 4 (two tile buffers), 6, 8, 10 (one), and beyond the path
+@pytest.mark.parametrize("nx,ny", [(400, 390), (512, 500), (600, 610), (720, 700), (850, 833), (1024, 1024),
+                                   (1100, 1050)])
+@pytest.mark.parametrize("prec,fields", [("fp64", False), ("fp64", True), ("mixed", False), ("mixed", True)])
+def test_rows_per_thread_vs_sweeps(torch_cuda, nx, ny, prec, fields):
+    """Against the second-run variant, whose iterations are sweep launches."""
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    prob = box(nx, ny, 1, 0, pulse_kind=1, pulse_e=(0.6, 0.8), a0=30.0, omega=1.0, t_pulse=0.02,
+               **(FIELDS if fields else {}))
+    gen = torch.Generator(device="cuda").manual_seed(nx + ny)
+    psi0 = torch.randn((2, ny, nx, 2), generator=gen, dtype=torch.float64, device="cuda")
+    psi0 = torch.view_as_complex(psi0).contiguous() / np.sqrt(4.0 * nx * ny)
+    n, dt, m = 3, 1e-4, 8
+    say(f"resident {nx}x{ny} {prec} fields={fields} against sweeps")
+    prop = Propagator(prob, m, prec)
+    a, b = psi0.clone(), psi0.clone()
+    sa = prop.step(a, 0.0, dt, n)
+    sb = prop.step(b, 0.0, dt, n, lowmem=True)
+    prop.close()
+    dist = float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b))
+    phase = dt * (C * C + 2 * C / 0.1 + 40 * C)
+    tol = 64 * n * phase * EPS
+    if prec == "mixed":  # each run lies within its own storage bound
+        tol += sa["cum_round_bound"][-1] + sb["cum_round_bound"][-1]
+        np.testing.assert_allclose(sa["round_bound"], sb["round_bound"], rtol=1e-6)
+    assert dist <= tol
+    assert np.array_equal(sa["k_eff"], sb["k_eff"])
+    np.testing.assert_allclose(sa["norm2"], sb["norm2"], rtol=64 * n * EPS + (1e-7 if prec == "mixed" else 0.0))
+
+
+def test_contexts_and_streams_at_once(torch_cuda):
+    """Two contexts of different grids on two streams, called from two threads,
+    equal their runs alone bit for bit."""
+    import threading
+
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    grids = [(512, 500), (130, 90)]
+    say("resident steps on two streams")
+    alone, jobs = [], []
+    for nx, ny in grids:
+        prob = box(nx, ny, 0, 0, **FIELDS)
+        psi0 = torch.from_numpy(packets.gaussian_packet(prob, 1.0, (1.0, 2.0))).cuda()
+        stream = torch.cuda.Stream()
+        prop = Propagator(prob, 9, "fp64", stream=stream)
+        torch.cuda.synchronize()
+        ref = psi0.clone()
+        torch.cuda.synchronize()
+        prop.step(ref, 0.0, 2e-4, 40)
+        alone.append(ref)
+        jobs.append((prop, psi0))
+    out = [None, None]
+
+    def work(i):
+        prop, psi0 = jobs[i]
+        res = []
+        for _ in range(5):
+            x = psi0.clone()
+            torch.cuda.synchronize()
+            prop.step(x, 0.0, 2e-4, 40)
+            res.append(x)
+        out[i] = res
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(2):
+        assert all(torch.equal(x, alone[i]) for x in out[i])
+        jobs[i][0].close()
