@@ -27,7 +27,11 @@
 // backward pass recomputes one segment of states at a time (the last segment
 // is still resident from the forward pass).  Per-step records (contraction,
 // both tridiagonal chains, shifts, k_eff) are written by the device and read
-// once per segment, so the host never waits inside a segment.
+// once per segment, so the host never waits inside a segment.  Grids that take
+// resident steps run a whole segment forward, and up to nlam steps backward, in
+// one launch each (512^2, m = 12, 100 steps: 44.0 -> 26.6 ms; as sweeps each step
+// was 14 launches of about 11 us); the contractions of those backward steps
+// follow from the bases the launch leaves.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -56,6 +60,8 @@ constexpr int kObserveBlocks = 1024;
 #define DL_ADJ_KEEP_GIB 32
 #endif
 constexpr size_t kKeepBasesBytes = size_t(DL_ADJ_KEEP_GIB) << 30;
+// Largest store of the bases of one resident backward launch.
+constexpr size_t kLamBasesBytes = size_t(8) << 30;
 
 struct AdjLayout {
     size_t sc = 0, alpha = 0, gamma = 0, obs = 0, fields = 0, cpart = 0, rec = 0, basis = 0, lam = 0,
@@ -74,6 +80,13 @@ struct AdjLayout {
     size_t kb_stride = 0, ks_stride = 0, ks_alpha = 0, ks_gamma = 0;
     size_t seg_slot = 0, kb_slot = 0, ks_slot = 0;  // bytes per slot
     int nfold = 1;  // contraction partial tables (one per backward step until the fold)
+    // grids that take resident steps: nlam backward steps run in one launch,
+    // which leaves their Krylov bases (lbasis), scalars (lscal) and states for
+    // the contractions after it (0: step by step, as sweeps); without kept
+    // bases the forward basis of a step is rebuilt by a launch of its own into
+    // the context's basis, its scalars in kscal, its end state in `spare`
+    int nlam = 0;
+    size_t lbasis = 0, lscal = 0, spare = 0;
 };
 
 AdjLayout adj_plan(const dl_params &p, int n_steps, int ckpt_every)
@@ -100,17 +113,21 @@ AdjLayout adj_plan(const dl_params &p, int n_steps, int ckpt_every)
     off = align256(off + sizeof(double) * 4 * dl::kBlock * (size_t)kContractBlocks * (size_t)A.nfold);
     A.rec = off;
     off = align256(off + sizeof(double) * dl::kRecLen * (size_t)A.seglen);
+    A.kb_stride = (size_t)(m - 1) * vec_stride(n, 16);
+    const bool resident = dl::resident_tiles(p.nx, p.ny, dl::kResidentWgs).rows > 0;
+    if (resident)
+        A.nlam = (int)std::max<size_t>(
+            1, std::min<size_t>((size_t)A.nfold, kLamBasesBytes / std::max<size_t>(A.kb_stride, 1)));
     A.basis = off;
     off += (size_t)(m - 1) * vec_stride(n, 16);
     A.lam = off;
-    off += 2 * vb;
-    A.kb_stride = (size_t)(m - 1) * vec_stride(n, 16);
+    off += (size_t)(std::max(A.nlam, 1) + 1) * vb;
     A.keep = A.kb_stride * (size_t)A.seglen <= kKeepBasesBytes;
     A.seg_slot = (size_t)(A.seglen + 1) * vb;
+    A.ks_alpha = align256(sizeof(dl::Scalars));
+    A.ks_gamma = A.ks_alpha + align256(sizeof(double) * (m + 3));
+    A.ks_stride = A.ks_gamma + align256(sizeof(double) * (m + 3));
     if (A.keep) {
-        A.ks_alpha = align256(sizeof(dl::Scalars));
-        A.ks_gamma = A.ks_alpha + align256(sizeof(double) * (m + 3));
-        A.ks_stride = A.ks_gamma + align256(sizeof(double) * (m + 3));
         A.kb_slot = A.kb_stride * (size_t)A.seglen;
         A.ks_slot = A.ks_stride * (size_t)A.seglen;
         const size_t per = A.kb_slot + A.ks_slot + A.seg_slot;
@@ -126,6 +143,20 @@ AdjLayout adj_plan(const dl_params &p, int n_steps, int ckpt_every)
         off += (size_t)A.nslot * A.kb_slot;
         A.kscal = off;
         off += (size_t)A.nslot * A.ks_slot;
+    }
+    if (A.nlam > 0) {
+        off = align256(off);
+        A.lbasis = off;
+        off += (size_t)A.nlam * A.kb_stride;
+        off = align256(off);
+        A.lscal = off;
+        off += (size_t)A.nlam * A.ks_stride;
+        if (!A.keep) {
+            A.kscal = off;
+            off = align256(off + A.ks_stride);
+            A.spare = off;
+            off += vb;
+        }
     }
     A.total = off;
     return A;
@@ -304,7 +335,30 @@ dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, 
     auto run_segment = [&](int g) -> dl_status {
         const int len = seg_len(g);
         DL_HIP(ctx, hipMemcpyAsync(seg(g, 0), ckpt(g), n * 16, hipMemcpyDeviceToDevice, st));
-        for (int i = 0; i < len; ++i) {
+        int first = 0;
+        while (first < len && A.nlam > 0 && ctx->resident.rows > 0) {
+            ResidentRun r;
+            r.psi[0] = r.psi[1] = seg(g, first);
+            r.state_stride = vb;
+            const Engine e0 = step_engine(g, first);
+            r.basis = e0.basis;
+            r.basis_step = A.keep ? A.kb_stride : 0;
+            r.vstride = vstride;
+            r.fields = fields + 4 * (size_t)(g * C + first);
+            r.field_stride = 4;
+            r.stats = dstat;
+            if (A.keep) {
+                r.keep = kept_scal(g, first);
+                r.keep_step = A.ks_stride;
+                r.keep_alpha = A.ks_alpha;
+                r.keep_gamma = A.ks_gamma;
+            }
+            int done = 0;
+            const dl_status s = run_resident(ctx, e0, opf, r, 0, std::min(len - first, dl::kChunk), &done);
+            if (s != DL_OK) return s;
+            first += done;
+        }
+        for (int i = first; i < len; ++i) {
             const double *fp = fields + 4 * (size_t)(g * C + i);
             const Engine ei = step_engine(g, i);
             const dl_status sb = run_build(ctx, ei, opf, seg(g, i), fp, partials, 1);
@@ -324,8 +378,9 @@ dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, 
         int status = 0;
         DL_HIP(ctx, hipMemcpyAsync(&status, &sc->status, sizeof(int), hipMemcpyDeviceToHost, st));
         DL_HIP(ctx, hipStreamSynchronize(st));
-        if (status != 0) return ctx->fail(DL_ERR_NONFINITE, std::string("non-finite Lanczos reduction in the ") + what);
-        return DL_OK;
+        if (status == 0) return DL_OK;
+        if (status == dl::kStatusTimeout) clear_failure(ctx, status);
+        return ctx->status_fail(status, std::string("in the ") + what);
     };
 
     // forward pass with checkpoints
@@ -366,33 +421,22 @@ dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, 
             const dl_status s = run_segment(g);
             if (s != DL_OK) return s;
         }
-        for (int i = len - 1; i >= 0; --i) {
-            const size_t ns = (size_t)g * C + i;
-            dl_status s = DL_OK;
-            const Engine ei = step_engine(g, i);
-            if (!A.keep) {
-                s = run_build(ctx, ei, opf, seg(g, i), fields + 4 * ns, partials, 1, true);
-                if (s != DL_OK) return s;
-            }
-            // the backward step first: its small exponential completes T of the
-            // lambda basis, and the recombination leaves the basis and lam(cur)
-            // for the contraction below
-            s = run_build(ctx, el, opb, lam(cur), fields + 4 * ns + 2, partials, 1);
-            if (s != DL_OK) return s;
-            s = run_finish(ctx, el, lam(cur), lam(1 - cur), dstat, partials);
-            if (s != DL_OK) return s;
+        // the contraction of step i: lambda basis, start state and scalars lb, l1
+        // and ls (alpha and gamma behind them as kept), psi likewise
+        auto contract = [&](int i, const double2 *l1, const char *lb, const dl::Scalars *ls, const double *la,
+                            const double *lg, bool kept) {
             dl::ContractArgs ca{};
-            ca.lam1 = lam(cur);
-            ca.lam_basis = el.basis;
+            ca.lam1 = l1;
+            ca.lam_basis = lb;
             ca.psi1 = seg(g, i);
-            ca.psi_basis = ei.basis;
+            ca.psi_basis = step_engine(g, i).basis;
             ca.vec_bytes = vstride;
             ca.sites = sites;
-            ca.sc_lam = el.sc;
-            ca.alpha_lam = el.alpha;
-            ca.gamma_lam = el.gamma;
-            if (A.keep) {
-                char *ks = kept_scal(g, i);
+            ca.sc_lam = ls;
+            ca.alpha_lam = la;
+            ca.gamma_lam = lg;
+            if (kept) {
+                const char *ks = A.keep ? kept_scal(g, i) : aw + A.kscal;
                 ca.sc_psi = reinterpret_cast<const dl::Scalars *>(ks);
                 ca.alpha_psi = reinterpret_cast<const double *>(ks + A.ks_alpha);
                 ca.gamma_psi = reinterpret_cast<const double *>(ks + A.ks_gamma);
@@ -410,11 +454,77 @@ dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, 
                 dl::launch_contract_fold(cpart, A.nfold, ncb, rec, i, pending, st);
                 pending = 0;
             }
+        };
+        for (int i = len - 1; i >= 0;) {
+            const size_t ns = (size_t)g * C + i;
+            dl_status s = DL_OK;
+            // backward steps i, i - 1, .. in one launch; without kept bases one
+            // step, after the forward basis of step i
+            if (A.nlam > 0 && ctx->resident.rows > 0) {
+                const int nb = A.keep ? std::min(i + 1, A.nlam) : 1;
+                int done = 0;
+                ResidentRun r;
+                r.vstride = vstride;
+                r.stats = dstat;
+                r.keep_alpha = A.ks_alpha;
+                r.keep_gamma = A.ks_gamma;
+                r.keep_step = A.ks_stride;
+                if (!A.keep) {
+                    r.psi[0] = seg(g, i);
+                    r.psi[1] = reinterpret_cast<double2 *>(aw + A.spare);
+                    r.basis = ep.basis;
+                    r.fields = fields + 4 * ns;
+                    r.keep = aw + A.kscal;
+                    s = run_resident(ctx, ep, opf, r, 0, 1, &done);
+                    if (s != DL_OK) return s;
+                }
+                if (A.keep || done == 1) {
+                    r.psi[0] = r.psi[1] = lam(0);
+                    r.state_stride = vb;
+                    r.basis = aw + A.lbasis;
+                    r.basis_step = A.kb_stride;
+                    r.fields = fields + 4 * ns + 2;
+                    r.field_stride = -4;
+                    r.keep = aw + A.lscal;
+                    s = run_resident(ctx, el, opb, r, 0, nb, &done);
+                    if (s != DL_OK) return s;
+                    if (done == nb) {
+                        for (int j = 0; j < nb; ++j) {
+                            const char *ks = aw + A.lscal + (size_t)j * A.ks_stride;
+                            contract(i - j, lam(j), r.basis + (size_t)j * A.kb_stride,
+                                     reinterpret_cast<const dl::Scalars *>(ks),
+                                     reinterpret_cast<const double *>(ks + A.ks_alpha),
+                                     reinterpret_cast<const double *>(ks + A.ks_gamma), true);
+                        }
+                        DL_HIP(ctx, hipMemcpyAsync(lam(0), lam(nb), n * 16, hipMemcpyDeviceToDevice, st));
+                        i -= nb;
+                        continue;
+                    }
+                }
+            }
+            const Engine ei = step_engine(g, i);
+            if (!A.keep) {
+                s = run_build(ctx, ei, opf, seg(g, i), fields + 4 * ns, partials, 1, true);
+                if (s != DL_OK) return s;
+            }
+            // the backward step first: its small exponential completes T of the
+            // lambda basis, and the recombination leaves the basis and lam(cur)
+            // for the contraction below
+            s = run_build(ctx, el, opb, lam(cur), fields + 4 * ns + 2, partials, 1);
+            if (s != DL_OK) return s;
+            s = run_finish(ctx, el, lam(cur), lam(1 - cur), dstat, partials);
+            if (s != DL_OK) return s;
+            contract(i, lam(cur), el.basis, el.sc, el.alpha, el.gamma, A.keep);
             cur = 1 - cur;
+            --i;
         }
         DL_HIP(ctx, hipGetLastError());
         DL_HIP(ctx, hipMemcpyAsync(hrec.data(), rec, sizeof(double) * dl::kRecLen * len, hipMemcpyDeviceToHost, st));
-        DL_HIP(ctx, hipStreamSynchronize(st));
+        // (a resident launch that fails leaves no records of its later steps)
+        for (const dl::Scalars *sc : {ep.sc, el.sc}) {
+            const dl_status s = check_status(sc, "backward pass");
+            if (s != DL_OK) return s;
+        }
         for (int i = 0; i < len; ++i) {
             const double *r = hrec.data() + (size_t)i * dl::kRecLen;
             if (r[dl::kRecMeta + 4] != 0.0 || r[dl::kRecMeta + 5] != 0.0)

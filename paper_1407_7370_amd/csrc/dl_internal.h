@@ -37,7 +37,7 @@ struct Scalars {
     // (0: m), and the small exponential predicts knext for the next step
     int kmin, kmax, knext;
     double ktol;                   // per-step bound on the error estimate (0: off)
-    unsigned int epoch;            // last epoch of the resident steps' exchange (never reset within a workspace)
+    unsigned int epoch;            // last epoch of the workspace's exchange buffers (resident steps; never reset)
     unsigned int pad;
 };
 // Scalars::status of a call whose resident step waited too long (0 ok, 3 a
@@ -190,6 +190,7 @@ struct ResidentArgs {
     char *keep;                // per step (keep_step apart): Scalars, alpha and gamma for the adjoint, or NULL
     size_t keep_step, keep_alpha, keep_gamma;
     unsigned long long *red, *halo;  // exchange buffers
+    unsigned int *epoch;             // their last epoch
     unsigned long long *ticks;       // per kernel class, the launch's 100 MHz ticks are added (timing), or NULL
     __host__ __device__ double2 *state_in(int s) const
     {

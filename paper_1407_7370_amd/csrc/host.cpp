@@ -371,6 +371,7 @@ dl_status run_resident(dl_context *ctx, const Engine &e, const dl::Op &op, const
     a.keep_gamma = r.keep_gamma;
     a.red = reinterpret_cast<unsigned long long *>(ws + L.comm);
     a.halo = reinterpret_cast<unsigned long long *>(ws + L.comm + dl::kCommRed);
+    a.epoch = &ctx->sc()->epoch;
     a.ticks = ctx->timing ? ticks_of(ctx) : nullptr;
     for (int i = 0; i < n; i += dl::kResidentSteps) {
         a.n_steps = std::min(dl::kResidentSteps, n - i);

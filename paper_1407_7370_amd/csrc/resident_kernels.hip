@@ -347,7 +347,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
     }
     unsigned long long *const red = a.red, *const halo = a.halo;
     const size_t halo_buf = (size_t)NW * NS * nwg;
-    uint32_t epoch = sc->epoch;
+    uint32_t epoch = *a.epoch;
     const unsigned long long started = wall_clock64();
 
     const bool direct = nwg <= kDirect;
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
             sc->status = timeout ? kStatusTimeout : 3;
             sc->kstop = -1;
         }
-        sc->epoch = epoch;
+        *a.epoch = epoch;
         if (a.ticks)
             for (int q = 0; q < 5; ++q) a.ticks[q] += clk[q];
     }

@@ -140,3 +140,21 @@ def test_contexts_and_streams_at_once(torch_cuda):
     for i in range(2):
         assert all(torch.equal(x, alone[i]) for x in out[i])
         jobs[i][0].close()
+
+
+def test_adjoint_without_kept_bases(torch_cuda):
+    """One segment too long for its Krylov bases to be kept (400 steps of 512^2,
+    m = 12: 37 GB): the backward pass rebuilds them step by step, and loss and
+    gradient equal those of short segments bit for bit."""
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    cfg = packets.fourier_pulse_512()
+    psi0 = torch.from_numpy(packets.initial_state(cfg)).cuda()
+    prop = Propagator(cfg["problem"], cfg["m"], "fp64")
+    res = []
+    for ckpt in (400, 50):
+        say(f"adjoint 512x512 400 steps, segments of {ckpt}")
+        res.append(prop.adjoint(psi0, 0.0, cfg["dt"], 400, ckpt, 9))
+    prop.close()
+    assert res[0][0] == res[1][0]
+    assert np.array_equal(res[0][1], res[1][1])
