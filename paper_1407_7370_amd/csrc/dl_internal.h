@@ -369,13 +369,19 @@ int sweep_terms(const Op &op);
 // points, n a multiple of 16 up to 64.
 struct HermOp {
     int n;
+    // 1: the problem is held in the parity basis of both axes (n = 32, 64).  The
+    // nodes are symmetric about 0, so D maps even functions to odd ones and back:
+    // index p < n/2 is the normalised even combination of nodes p and n-1-p, p >=
+    // n/2 the odd one of nodes p - n/2 and its mirror, and D has two n/2 x n/2
+    // blocks, half the products
+    int split;
     int pot_kind;        // 0 none, 1 -vz / sqrt(r^2 + va2)
     double c, chi;       // speed of light, alpha2 = chi sigma2
     double mc2;          // m c^2
     double bq;           // c q B / 2 (symmetric gauge)
     double vz, va2;
-    const double *dmat;  // D~ / scale, n x n row-major (device)
-    const double *x;     // scaled nodes (device)
+    const double *dmat;  // D~ / scale, n x n row-major (device), in the problem's basis
+    const double *x;     // scaled nodes (device); split: node p mod n/2 at index p
 };
 struct HermRun {
     const double2 *b;    // start vector (device, layout (2, n, n))
@@ -385,6 +391,17 @@ struct HermRun {
 };
 void launch_herm_apply(const HermOp *ops, const double2 *const *x, double2 *const *y, int n, hipStream_t st);
 void launch_herm_lanczos(const HermOp *ops, HermRun *runs, int n, int k_max, hipStream_t st);
+// Ritz values of the leading blocks T_j, j = every, 2 every, .. and k_eff, of
+// every problem in its window (lo, hi] (windows: lo, hi per problem): for problem
+// i and checkpoint c the kHermRitzLen doubles at out + (i ncheck + c)
+// kHermRitzLen hold their number (-1: more than kHermRitzMax, or a T too small
+// for the kernel), beta_j, the values ascending and the last component of their
+// unit eigenvectors.  k_max <= kHermRitzK.
+constexpr int kHermRitzMax = 16;
+constexpr int kHermRitzLen = 2 + 2 * kHermRitzMax;
+constexpr int kHermRitzK = 2048;
+void launch_herm_ritz(const HermRun *runs, const double *windows, int n, int k_max, int every, int ncheck, double *out,
+                      hipStream_t st);
 
 // Eigen mode with full reorthogonalisation (eigen_kernels.hip).  Stored
 // complex128 vectors q_1..q_K at q + (j-1) * vstride; the projection partial

@@ -104,19 +104,41 @@ const std::vector<double> &cached_nodes(int n)
     return it->second;
 }
 
-void tables(const dl_hermite_params &p, double *dm, double *x)
+// Whether the recurrence of a problem runs in the parity basis: the blocks of D
+// are whole 16 x 16 tiles.
+bool parity_basis(const dl_hermite_params &p) { return p.n % 32 == 0; }
+
+// split: D and the nodes in the parity basis (dl::HermOp::split).  With E, O the
+// even and odd combinations of nodes i, j < n/2 (xi_(n-1-j) = -xi_j),
+//   D_OE[i][j] = D_ij + D_i,n-1-j = (-1)^(i+j) 2 xi_j / (xi_i^2 - xi_j^2), diagonal -1 / (2 xi_i)
+//   D_EO[i][j] = D_ij - D_i,n-1-j = (-1)^(i+j) 2 xi_i / (xi_i^2 - xi_j^2), diagonal  1 / (2 xi_i)
+void tables(const dl_hermite_params &p, bool split, double *dm, double *x)
 {
     const std::vector<double> xi = cached_nodes(p.n);
-    for (int i = 0; i < p.n; ++i)
-        for (int j = 0; j < p.n; ++j)
-            dm[(size_t)i * p.n + j] = i == j ? 0.0 : (((i + j) & 1) ? -1.0 : 1.0) / ((xi[i] - xi[j]) * p.scale);
-    for (int i = 0; i < p.n; ++i) x[i] = xi[i] * p.scale;
+    const int n = p.n, h = n / 2;
+    if (!split) {
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j)
+                dm[(size_t)i * n + j] = i == j ? 0.0 : (((i + j) & 1) ? -1.0 : 1.0) / ((xi[i] - xi[j]) * p.scale);
+        for (int i = 0; i < n; ++i) x[i] = xi[i] * p.scale;
+        return;
+    }
+    for (int i = 0; i < h; ++i)
+        for (int j = 0; j < h; ++j) {
+            const double w = (((i + j) & 1) ? -2.0 : 2.0) / ((xi[i] - xi[j]) * (xi[i] + xi[j]) * p.scale);
+            const double dg = 0.5 / (xi[i] * p.scale);
+            dm[(size_t)i * n + j] = dm[(size_t)(h + i) * n + h + j] = 0.0;
+            dm[(size_t)(h + i) * n + j] = i == j ? -dg : w * xi[j];
+            dm[(size_t)i * n + h + j] = i == j ? dg : w * xi[i];
+        }
+    for (int i = 0; i < h; ++i) x[i] = x[h + i] = xi[i] * p.scale;
 }
 
-dl::HermOp make_hop(const dl_hermite_params &p, const double *dmat, const double *x)
+dl::HermOp make_hop(const dl_hermite_params &p, bool split, const double *dmat, const double *x)
 {
     dl::HermOp o{};
     o.n = p.n;
+    o.split = split;
     o.c = p.c;
     o.chi = p.chirality < 0 ? -1.0 : 1.0;
     o.mc2 = p.mass * p.c * p.c;
@@ -134,11 +156,12 @@ dl::HermOp make_hop(const dl_hermite_params &p, const double *dmat, const double
     return o;
 }
 
-// Workspace: the problem table, the run table, the pointer table and the
-// per-problem D and nodes (one block, uploaded in one copy), then the alpha
+// Workspace: the problem table, the run table, the pointer table, the windows and
+// the per-problem D and nodes (one block, uploaded in one copy), then the alpha
 // and beta arrays of every problem (one block, downloaded in one copy).
 struct HermLayout {
-    size_t ops = 0, runs = 0, ptrs = 0, tables_end = 0, ab0 = 0, total = 0;
+    size_t ops = 0, runs = 0, ptrs = 0, win = 0, tables_end = 0, ab0 = 0, ritz = 0, total = 0;
+    int ncheck = 0;  // checkpoints whose Ritz values the device computes (0: the host does)
     std::vector<size_t> dmat, x, ab;
 };
 
@@ -152,6 +175,8 @@ HermLayout herm_plan(const dl_hermite_params *p, int np, int k_max)
     off = align256(off + sizeof(dl::HermRun) * np);
     L.ptrs = off;
     off = align256(off + sizeof(void *) * 2 * np);
+    L.win = off;
+    off = align256(off + sizeof(double) * 2 * np);
     for (int i = 0; i < np; ++i) {
         const size_t n2 = (size_t)p[i].n * p[i].n;
         L.dmat.push_back(off);
@@ -165,7 +190,13 @@ HermLayout herm_plan(const dl_hermite_params *p, int np, int k_max)
         L.ab.push_back(off);
         off += sizeof(double) * 2 * (size_t)std::max(k_max, 1);
     }
-    L.total = align256(off);
+    off = align256(off);
+    if (k_max <= dl::kHermRitzK) {
+        L.ncheck = (k_max + kEigenCheckEvery - 1) / kEigenCheckEvery;
+        L.ritz = off;
+        off = align256(off + sizeof(double) * dl::kHermRitzLen * (size_t)L.ncheck * np);
+    }
+    L.total = off;
     return L;
 }
 
@@ -207,8 +238,8 @@ dl_status dirac_lanczos_hermite_apply(const dl_hermite_params *params, const voi
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     char *ws = static_cast<char *>(workspace);
     std::vector<char> img(L.tables_end, 0);
-    tables(*params, reinterpret_cast<double *>(img.data() + L.dmat[0]), reinterpret_cast<double *>(img.data() + L.x[0]));
-    const dl::HermOp op = make_hop(*params, reinterpret_cast<double *>(ws + L.dmat[0]),
+    tables(*params, false, reinterpret_cast<double *>(img.data() + L.dmat[0]), reinterpret_cast<double *>(img.data() + L.x[0]));
+    const dl::HermOp op = make_hop(*params, false, reinterpret_cast<double *>(ws + L.dmat[0]),
                                    reinterpret_cast<double *>(ws + L.x[0]));
     const void *ptrs[2] = {x, y};
     std::memcpy(img.data() + L.ops, &op, sizeof(op));
@@ -247,10 +278,15 @@ dl_status dirac_lanczos_hermite_eigen(const dl_hermite_params *params, int32_t n
     std::vector<char> img(L.tables_end, 0);
     dl::HermOp *ops = reinterpret_cast<dl::HermOp *>(img.data() + L.ops);
     dl::HermRun *runs0 = reinterpret_cast<dl::HermRun *>(img.data() + L.runs);
+    double *win = reinterpret_cast<double *>(img.data() + L.win);
     for (int i = 0; i < n_problems; ++i) {
-        tables(params[i], reinterpret_cast<double *>(img.data() + L.dmat[i]),
+        const bool split = parity_basis(params[i]);
+        tables(params[i], split, reinterpret_cast<double *>(img.data() + L.dmat[i]),
                reinterpret_cast<double *>(img.data() + L.x[i]));
-        ops[i] = make_hop(params[i], reinterpret_cast<double *>(ws + L.dmat[i]), reinterpret_cast<double *>(ws + L.x[i]));
+        ops[i] = make_hop(params[i], split, reinterpret_cast<double *>(ws + L.dmat[i]),
+                          reinterpret_cast<double *>(ws + L.x[i]));
+        win[2 * i] = e_lo[i];
+        win[2 * i + 1] = e_hi[i];
         dl::HermRun r{};
         r.b = static_cast<const double2 *>(psi0[i]);
         r.alpha = reinterpret_cast<double *>(ws + L.ab[i]);
@@ -261,31 +297,60 @@ dl_status dirac_lanczos_hermite_eigen(const dl_hermite_params *params, int32_t n
         return herm_fail(DL_ERR_DEVICE, "upload of the problem tables failed");
     dl::launch_herm_lanczos(reinterpret_cast<const dl::HermOp *>(ws + L.ops), reinterpret_cast<dl::HermRun *>(ws + L.runs),
                             n_problems, k_max, st);
+    const dl::HermRun *d_runs = reinterpret_cast<const dl::HermRun *>(ws + L.runs);
+    if (L.ncheck > 0)
+        dl::launch_herm_ritz(d_runs, reinterpret_cast<const double *>(ws + L.win), n_problems, k_max, kEigenCheckEvery,
+                             L.ncheck, reinterpret_cast<double *>(ws + L.ritz), st);
     if (hipGetLastError() != hipSuccess) return herm_fail(DL_ERR_DEVICE, "kernel launch failed");
-    std::vector<double> ab((size_t)2 * k_max * n_problems);
+    std::vector<double> ritz((size_t)dl::kHermRitzLen * L.ncheck * n_problems), ab;
     std::vector<dl::HermRun> runs(n_problems);
-    if (hipMemcpyAsync(ab.data(), ws + L.ab0, sizeof(double) * ab.size(), hipMemcpyDeviceToHost, st) != hipSuccess ||
+    if ((!ritz.empty() &&
+         hipMemcpyAsync(ritz.data(), ws + L.ritz, sizeof(double) * ritz.size(), hipMemcpyDeviceToHost, st) != hipSuccess) ||
         hipMemcpyAsync(runs.data(), ws + L.runs, sizeof(dl::HermRun) * n_problems, hipMemcpyDeviceToHost, st) !=
             hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return herm_fail(DL_ERR_DEVICE, "synchronisation failed");
-    bool nonfinite = false;
+    // problems that the device's Ritz step did not take (long recurrences,
+    // windows with many values) are solved here from their T
+    auto record = [&](int i, int c) { return ritz.data() + ((size_t)i * L.ncheck + c) * dl::kHermRitzLen; };
+    std::vector<char> here(n_problems, L.ncheck == 0);
+    bool nonfinite = false, any_here = L.ncheck == 0;
     for (int i = 0; i < n_problems; ++i) {
         if (runs[i].keff < 0) nonfinite = true;
         n_found[i] = 0;
+        for (int c = 0; c < L.ncheck && !here[i] && runs[i].keff > 0; ++c) here[i] = record(i, c)[0] < 0.0;
+        any_here = any_here || here[i];
+    }
+    if (any_here) {
+        ab.resize((size_t)2 * k_max * n_problems);
+        if (hipMemcpyAsync(ab.data(), ws + L.ab0, sizeof(double) * ab.size(), hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return herm_fail(DL_ERR_DEVICE, "synchronisation failed");
     }
     // converged clusters accumulated over the leading blocks k = 64, 128, ...
     // and k; problems are independent and spread over host threads
     std::atomic<int> next{0};
-    const int nt = std::max(1, std::min<int>(n_problems, host_threads()));
+    const int nt = any_here ? std::max(1, std::min<int>(n_problems, host_threads())) : 1;
     const int per_problem = std::max(1, host_threads() / nt);  // a few problems: checkpoints in parallel too
     auto worker = [&] {
         for (int i; (i = next.fetch_add(1)) < n_problems;) {
             const int k = runs[i].keff;
             if (k <= 0) continue;
-            const double *al = ab.data() + (size_t)2 * k_max * i, *be = al + k_max;
             std::vector<std::pair<double, double>> found;
-            converged_union(al, be, k, e_lo[i], e_hi[i], tol, kEigenCheckEvery, per_problem, found);
+            if (here[i]) {
+                const double *al = ab.data() + (size_t)2 * k_max * i, *be = al + k_max;
+                converged_union(al, be, k, e_lo[i], e_hi[i], tol, kEigenCheckEvery, per_problem, found);
+            } else {
+                for (int c = 0; c * kEigenCheckEvery < k; ++c) {
+                    const double *r = record(i, c);
+                    const int nw = (int)r[0];
+                    const std::vector<double> lam(r + 2, r + 2 + nw),
+                        zl(r + 2 + dl::kHermRitzMax, r + 2 + dl::kHermRitzMax + nw);
+                    double ev[dl::kHermRitzMax], bd[dl::kHermRitzMax];
+                    const int nf = ritz_select(lam, zl, r[1], e_lo[i], e_hi[i], tol, dl::kHermRitzMax, ev, bd, nullptr);
+                    merge_converged(found, ev, bd, nf, tol);
+                }
+            }
             const int nf = std::min((int)found.size(), n_wanted);
             for (int r = 0; r < nf; ++r) {
                 evals[(size_t)i * n_wanted + r] = found[r].first;

@@ -113,28 +113,6 @@ struct SitePot {
 template <int K>
 struct SitePot<K, 0> {};
 
-// Sum over the 16 lanes of a row by lane permutations (every lane ends with the
-// same bits).
-__device__ __forceinline__ double row_sum(double v)
-{
-#define DL_DPP_ADD(ctrl)                                                                                       \
-    v += __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xF, 0xF, true),                   \
-                          __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xF, 0xF, true))
-    DL_DPP_ADD(0xB1);   // lanes 1 apart
-    DL_DPP_ADD(0x4E);   // 2 apart
-    DL_DPP_ADD(0x141);  // the other half of eight
-    DL_DPP_ADD(0x140);  // the other half of sixteen
-#undef DL_DPP_ADD
-    return v;
-}
-__device__ __forceinline__ double lanes_sum(double v)
-{
-    v = row_sum(v);
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    return v;
-}
-
 // 1.0 where bit k of the mask is set, else 0.0.
 __device__ __forceinline__ double bit_one(uint32_t mask, int k)
 {
