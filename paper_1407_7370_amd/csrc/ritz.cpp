@@ -9,6 +9,7 @@
 #include <cfloat>
 #include <cmath>
 #include <cstdint>
+#include <system_error>
 #include <thread>
 
 namespace dlh {
@@ -17,8 +18,12 @@ void tridiag_full(std::vector<double> d, std::vector<double> e, std::vector<doub
                   std::vector<double> &v)
 {
     const int k = (int)d.size();
-    v.assign((size_t)k * k, 0.0);
-    for (int i = 0; i < k; ++i) v[(size_t)i * k + i] = 1.0;
+    // the rotations of the sweeps, applied to the eigenvectors afterwards
+    struct Rot {
+        int q;
+        double c, s;
+    };
+    std::vector<Rot> rot;
     e.resize(k, 0.0);
     const double eps = 2.220446049250313e-16;
     int h = k - 1, iter = 0;
@@ -55,15 +60,46 @@ void tridiag_full(std::vector<double> d, std::vector<double> e, std::vector<doub
                 z = -s * bq1;
                 e[q + 1] = c * bq1;
             }
-            for (int row = 0; row < k; ++row) {
-                double &zq = v[(size_t)row * k + q], &zq1 = v[(size_t)row * k + q + 1];
-                const double a0 = zq, a1 = zq1;
-                zq = c * a0 - s * a1;
-                zq1 = s * a0 + c * a1;
-            }
+            rot.push_back(Rot{q, c, s});
         }
     }
     lam = d;
+    v.resize((size_t)k * k);
+    // Every row of v takes the same rotations in the same order, so blocks of
+    // rows are independent: each is held as contiguous columns (a rotation runs
+    // along two of them at full vector width), large problems on several threads.
+    // k = 512: 0.95 s rotating the rows of v in place, 0.16 s by columns, 0.05 s
+    // by blocks on eight threads.
+    constexpr int kRows = 32;
+    auto block = [&](int r0) {
+        const int n = std::min(kRows, k - r0);
+        std::vector<double> col((size_t)k * kRows, 0.0);
+        for (int i = 0; i < n; ++i) col[(size_t)(r0 + i) * kRows + i] = 1.0;
+        for (const Rot &r : rot) {
+            double *__restrict__ zq = col.data() + (size_t)r.q * kRows, *__restrict__ zq1 = zq + kRows;
+            const double c = r.c, s = r.s;
+            for (int row = 0; row < kRows; ++row) {
+                const double a0 = zq[row], a1 = zq1[row];
+                zq[row] = c * a0 - s * a1;
+                zq1[row] = s * a0 + c * a1;
+            }
+        }
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < k; ++j) v[(size_t)(r0 + i) * k + j] = col[(size_t)j * kRows + i];
+    };
+    const int blocks = (k + kRows - 1) / kRows;
+    const int nt = std::min(blocks, k >= 128 ? host_threads() : 1);
+    std::atomic<int> next{0};
+    auto worker = [&] {
+        for (int b; (b = next.fetch_add(1)) < blocks;) block(b * kRows);
+    };
+    std::vector<std::thread> pool;
+    try {
+        for (int t = 1; t < nt; ++t) pool.emplace_back(worker);
+    } catch (const std::system_error &) {  // no more threads: the ones there do the work
+    }
+    worker();
+    for (auto &th : pool) th.join();
 }
 
 namespace {
