@@ -39,7 +39,7 @@ Layout plan(const dl_params &p, int mode, int k_eigen);
 // coefficient arrays (k complex each), the projection partial table and the
 // staged eigenvector columns of the Ritz vectors.
 struct ReorthLayout {
-    size_t z = 0, q = 0, h1 = 0, h2 = 0, pproj = 0, tsel = 0, total = 0;
+    size_t z = 0, q = 0, h = 0, pproj = 0, tsel = 0, total = 0;
 };
 inline ReorthLayout reorth_layout(size_t n, int k)
 {
@@ -50,9 +50,7 @@ inline ReorthLayout reorth_layout(size_t n, int k)
     off += vs;
     R.q = off;
     off += (size_t)k * vs;
-    R.h1 = off;
-    off += align256(sizeof(double) * 2 * (size_t)k);
-    R.h2 = off;
+    R.h = off;
     off += align256(sizeof(double) * 2 * (size_t)k);
     R.pproj = off;
     off += align256(sizeof(double) * 2 * (size_t)dl::proj_tiles(n) * (size_t)k);

@@ -38,7 +38,7 @@ struct Scalars {
     int kmin, kmax, knext;
     double ktol;                   // per-step bound on the error estimate (0: off)
     unsigned int epoch;            // last epoch of the workspace's exchange buffers (resident steps; never reset)
-    unsigned int pad;
+    int again;                     // full reorthogonalisation: a second pass follows
 };
 // Scalars::status of a call whose resident step waited too long (0 ok, 3 a
 // non-finite reduction).
@@ -413,19 +413,22 @@ inline int proj_tiles(size_t nelem)
     const size_t t = (nelem + kBlock - 1) / kBlock;
     return (int)(t < (size_t)kProjTiles ? (t < 1 ? 1 : t) : (size_t)kProjTiles);
 }
-// h = Q[0..nvec)^H z (complex, fixed-order reduction).
-void launch_proj(const char *q, size_t vstride, int nvec, const double2 *z, size_t nelem, double *pproj,
-                 double *h, hipStream_t st);
-// z -= Q[0..nvec) h.
-void launch_sub_q(const char *q, size_t vstride, int nvec, const double *h, double2 *z, size_t nelem,
-                  int nblocks, hipStream_t st);
+// w = H q_i - alpha_i q_i - beta_{i-1} q_{i-1} (qm = q_{i-1}, not read for i = 1);
+// alpha_i into alpha[i].  op without homogeneous field.
+void launch_lanczos_local(const Op &op, const double2 *q, const double2 *qm, double2 *w, int i, double *alpha,
+                          const double *beta, const Scalars *sc, double *partials, int nblocks, hipStream_t st);
+// h = Q[0..nvec)^H z (complex, fixed-order reduction), z -= Q h, then beta_nvec =
+// ||z|| and the breakdown test, unless a second pass has to follow (Scalars::again),
+// which the call with `second` does where the flag asks for it.
+void launch_orth(const char *q, size_t vstride, int nvec, double2 *z, size_t nelem, double *pproj, double *h,
+                 const double *alpha, double *beta, Scalars *sc, double *partials, int nblocks, bool second,
+                 hipStream_t st);
 // beta_0 = ||psi||, q_1 = psi / beta_0 (kstop = 0 when psi = 0).
 void launch_first_q(const double2 *psi, size_t nelem, double2 *q1, Scalars *sc, double *beta, double *partials,
                     int nblocks, hipStream_t st);
-// beta_i = ||z||, alpha_i = Re h1_i, breakdown test; then q_{i+1} = z / beta_i
-// when i < k and the recurrence goes on.
-void launch_norm_next(const double2 *z, size_t nelem, const double *h1, int i, int k, double *alpha, double *beta,
-                      Scalars *sc, double *partials, double2 *qn, int nblocks, hipStream_t st);
+// q_{i+1} = z / beta_i while the recurrence goes on.
+void launch_next_q(const double2 *z, size_t nelem, int i, const double *beta, const Scalars *sc, double2 *qn,
+                   int nblocks, hipStream_t st);
 // Y[:, v] = Q[0..nvec) t[:, v] for v < r <= kRitzVecs (t: nvec x kRitzVecs
 // row-major, real), y_v at y + v * nelem.
 void launch_ritz(const char *q, size_t vstride, int nvec, const double *t, int r, double2 *y, size_t nelem,

@@ -3,17 +3,17 @@
 //
 // Sec. 2: the Lanczos vectors lose orthogonality once Ritz values converge,
 // which shows up as copies of converged values; orthogonalising every new
-// vector against all stored ones, twice, prevents it.  Iteration i:
-//   z = H q_i
-//   h1 = Q_i^H z;  z -= Q_i h1      (first pass; removes alpha_i q_i and
-//   h2 = Q_i^H z;  z -= Q_i h2       beta_{i-1} q_{i-1} as well)
-//   alpha_i = Re h1_i,  beta_i = ||z||,  q_{i+1} = z / beta_i
+// vector against all stored ones, twice where the first pass does not already
+// leave it orthogonal to rounding (eigen_kernels.hip), prevents it.  Iteration i:
+//   z = H q_i - alpha_i q_i - beta_{i-1} q_{i-1},  alpha_i = Re <q_i, H q_i>
+//   h = Q_i^H z;  z -= Q_i h       (and once more where h was not negligible)
+//   beta_i = ||z||,  q_{i+1} = z / beta_i
 // Ritz values and bounds follow eq. A_approx and eq. error_est (as in the
 // plain mode); the Ritz vectors are y = Q_k t (eq. eigenvec_approx).
 //
 // Everything between the start vector and the Ritz vectors stays on the
 // device: the scalars of the recurrence are updated by the last workgroup of
-// the norm reduction, and the host reads the breakdown flag every
+// the update z -= Q h, and the host reads the breakdown flag every
 // kPollEvery iterations only (iterations past a breakdown are skipped by the
 // kernels: their scalar updates are masked).  Every kEigenCheckEvery
 // iterations the host also computes the Ritz values of T and stops once
@@ -52,8 +52,7 @@ dl_status eigen_reorth(dl_context *ctx, const void *psi0, int k_max, double e_lo
     double2 *z = reinterpret_cast<double2 *>(vreg + R.z);
     char *Q = vreg + R.q;
     auto qv = [&](int j) { return reinterpret_cast<double2 *>(Q + (size_t)(j - 1) * vs); };  // q_j, 1-based
-    double *h1 = reinterpret_cast<double *>(vreg + R.h1);
-    double *h2 = reinterpret_cast<double *>(vreg + R.h2);
+    double *h = reinterpret_cast<double *>(vreg + R.h);
     double *pproj = reinterpret_cast<double *>(vreg + R.pproj);
     double *tsel = reinterpret_cast<double *>(vreg + R.tsel);
     hipStream_t st = ctx->stream;
@@ -95,13 +94,10 @@ dl_status eigen_reorth(dl_context *ctx, const void *psi0, int k_max, double e_lo
                 }
             }
         }
-        dl::launch_apply(op, ctx->tiles_apply, qv(i), z, 0.0, 0.0, st);
-        dl::launch_proj(Q, vs, i, z, n, pproj, h1, st);
-        dl::launch_sub_q(Q, vs, i, h1, z, n, nb, st);
-        dl::launch_proj(Q, vs, i, z, n, pproj, h2, st);
-        dl::launch_sub_q(Q, vs, i, h2, z, n, nb, st);
-        dl::launch_norm_next(z, n, h1, i, k_max, alpha, beta, sc, partials, i < k_max ? qv(i + 1) : nullptr, nb,
-                             st);
+        dl::launch_lanczos_local(op, qv(i), i > 1 ? qv(i - 1) : nullptr, z, i, alpha, beta, sc, partials, nb, st);
+        for (const bool second : {false, true})
+            dl::launch_orth(Q, vs, i, z, n, pproj, h, alpha, beta, sc, partials, nb, second, st);
+        if (i < k_max) dl::launch_next_q(z, n, i, beta, sc, qv(i + 1), nb, st);
         DL_HIP(ctx, hipGetLastError());
     }
     {

@@ -3,13 +3,27 @@
 // orthogonalised against all of them, twice) and of the Ritz vectors
 // (Sec. 2 eq. eigenvec_approx).
 //
-// Classical Gram-Schmidt in two passes (CGS2): h = Q^H z, z -= Q h, twice.
-// The projections of a pass all use the same z, so one pass is a
-// tall-skinny product that streams the stored basis once; the modified form
-// would stream it once per vector.  Every kernel here is bound by HBM
-// bandwidth: per pass, the projection reads the i stored vectors and z, the
-// update reads them again and rewrites z.  Reductions are per-workgroup
-// partials folded in a fixed order, so results are bitwise reproducible.
+// Iteration i: z = H q_i - alpha_i q_i - beta_{i-1} q_{i-1} (k_eig_apply,
+// k_local), then classical Gram-Schmidt, h = Q^H z, z -= Q h.  The projections of
+// a pass all use the same z, so one pass is a tall-skinny product that streams
+// the stored basis once; the modified form would stream it once per vector.
+//
+// A second pass follows where the first one removed anything to speak of:
+// ||h|| > kAgain ||z|| (the test of Daniel, Gragg, Kaufman and Stewart 1976).  What a
+// pass leaves along Q is (I - Q^H Q) h and its rounding, so with Q orthonormal to
+// d it is at most d ||h|| + O(eps ||z||): after the local terms h is the rounding of
+// H q_i (||h|| ~ eps ||H||) and one pass leaves O(eps), except near a breakdown,
+// where ||z|| itself is that small.  Without the local terms first (h_i = alpha_i,
+// far larger than ||z||) every iteration needed both passes.
+//
+// Bound by HBM bandwidth: the projection reads the i stored vectors and z, the
+// update reads them again and rewrites z.  The projection walks the basis upwards
+// and the update downwards, so that each finds what the other read last in the
+// last-level cache (3 % at 1024^2, 5 % at 256^2).  256^2, 512 vectors (1 GB): k_proj
+// 4.5 -> 5.7 TB/s, k_sub_q 5.8, a pass of 512 iterations with two Ritz vectors
+// 236 ms with two pairs of kernels an iteration, 115 ms now.
+// Reductions are per-workgroup partials folded in a fixed order, so results are
+// bitwise reproducible.
 //
 // Vectors use the state layout (complex128, both spinor planes), vector j
 // (0-based) of the basis at q + j * vstride bytes.
@@ -19,20 +33,19 @@
 
 #include "device_reduce.h"
 #include "dl_internal.h"
+#include "sweeps.h"
 
 namespace dl {
 namespace {
 
-#ifndef DL_DOT_VECS
-#define DL_DOT_VECS 16
-#endif
-#ifndef DL_PROJ_WORKGROUPS
-#define DL_PROJ_WORKGROUPS 8192
-#endif
-constexpr int kDotVecs = DL_DOT_VECS;  // basis vectors per workgroup of a projection
-// workgroups of a projection launch (at most kProjTiles per vector chunk);
-// measured on 1024^2 with K = 500: 2048 -> 3.30 s, 4096 -> 3.26 s, 8192 -> 3.21 s
-constexpr int kProjWorkgroups = DL_PROJ_WORKGROUPS;
+constexpr int kDotVecs = 16;  // basis vectors per workgroup of a projection
+// workgroups of a projection (at most kProjTiles per vector chunk): one resident
+// round of six per compute unit.  TB/s of 256^2 / 1024^2 (vector counts to 512 /
+// 256): 1024 5.38 / 5.79, 1536 5.73 / 5.98, 2048 5.06 / 5.26, 8192 5.49 / 5.80
+constexpr int kProjWorkgroups = 1536;
+constexpr int kProjSecond = 512;  // of the second pass, most of whose launches return at once
+// largest ||h|| / ||z|| of a pass that needs no second one
+constexpr double kAgain = 1.0 / 128.0;
 constexpr int kSubChunk = 256;  // coefficients staged in LDS per chunk of the update
 static_assert(kSubChunk % kDotVecs == 0, "the update pads a chunk to whole groups of kDotVecs");
 constexpr int kRitzChunk = 64;  // basis rows of t staged in LDS per chunk
@@ -42,19 +55,97 @@ __device__ __forceinline__ const double2 *qvec(const char *q, size_t vstride, in
     return reinterpret_cast<const double2 *>(q + (size_t)j * vstride);
 }
 
+// Sums of 2 N values over the wave's lanes: each step halves the values a lane
+// holds and the lanes that share them (for 32 values 32 exchanges; a butterfly
+// per value takes 192).  With 32 values lane l ends with the sum of value l >> 1.
+template <int N, int S>
+__device__ __forceinline__ double wave_sum_spread(double (&v)[2 * N])
+{
+    const bool up = ((int)threadIdx.x & S) != 0;
+    double r[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const double keep = up ? v[k + N] : v[k], send = up ? v[k] : v[k + N];
+        r[k] = keep + __shfl_xor(send, S, 64);
+    }
+    if constexpr (N > 1)
+        return wave_sum_spread<N / 2, S / 2>(r);
+    else
+        return r[0] + __shfl_xor(r[0], S / 2, 64);
+}
+
+// w = H q (one site per thread and step), and this workgroup's partial of
+// alpha = Re <q, w>.
+__global__ __launch_bounds__(kBlock) void k_eig_apply(Op op, const double2 *__restrict__ q, double2 *__restrict__ w,
+                                                      double *__restrict__ partials)
+{
+    const size_t sites = (size_t)op.nx * op.ny;
+    double acc[1] = {0.0};
+    for (size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x; e < sites; e += (size_t)gridDim.x * kBlock) {
+        const int j = (int)(e / (unsigned)op.nx), i = (int)(e - (size_t)j * op.nx);
+        auto site = [&](int x, int y, bool in, bool periodic) {
+            if (!in && !periodic) return sp_zero();
+            const size_t g = (size_t)y * op.nx + x;
+            const double2 a = q[g], b = q[sites + g];
+            return Sp{a.x, a.y, b.x, b.y};
+        };
+        const Sp c = site(i, j, true, true);
+        const Sp l = site(i > 0 ? i - 1 : op.nx - 1, j, i > 0, op.bcx), r = site(i + 1 < op.nx ? i + 1 : 0, j, i + 1 < op.nx, op.bcx);
+        const Sp d = site(i, j > 0 ? j - 1 : op.ny - 1, j > 0, op.bcy), u = site(i, j + 1 < op.ny ? j + 1 : 0, j + 1 < op.ny, op.bcy);
+        LaneGeo lg{};
+        lg.colw = i;
+        lg.inx = true;
+        lg.x = op.xmin + i * op.hx;
+        const double y = op.ymin + j * op.hy;
+        const Sp o = hop(op, c, l, r, d, u, site_pot_row(op, lg, j, y), op.bq * y, -op.bqy * lg.x);
+        w[e] = make_double2(o.r0, o.i0);
+        w[sites + e] = make_double2(o.r1, o.i1);
+        acc[0] += sp_redot(c, o);
+    }
+    store_partial(acc, partials, (int)blockIdx.x);
+}
+
+// alpha_i from the partials, and w -= alpha_i q_i + beta_{i-1} q_{i-1}.
+__global__ __launch_bounds__(kBlock) void k_local(const double2 *__restrict__ q, const double2 *__restrict__ qm,
+                                                  double2 *__restrict__ w, size_t nelem, int i, double *alpha,
+                                                  const double *beta, const Scalars *sc,
+                                                  const double *partials, int npart)
+{
+    __shared__ double red[kWaves][1];
+    double tot[1];
+    fold_partials(partials, npart, red, tot);
+    const double al = tot[0], be = i > 1 ? beta[i - 1] : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0 && sc->kstop >= i) alpha[i] = al;
+    for (size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x; e < nelem; e += (size_t)gridDim.x * kBlock) {
+        const double2 a = q[e];
+        double2 v = w[e];
+        v.x -= al * a.x;
+        v.y -= al * a.y;
+        if (i > 1) {
+            const double2 b = qm[e];
+            v.x -= be * b.x;
+            v.y -= be * b.y;
+        }
+        w[e] = v;
+    }
+}
+
 // Partial projections.  Workgroup (t, c) accumulates conj(q_j) . z over the
 // elements t*256 + tid + r * ntiles*256 for the 16 vectors j = 16c .. 16c+15
 // (< nvec) and writes them to pproj[(j * ntiles + t) * 2 + {re, im}].
 __global__ __launch_bounds__(kBlock) void k_proj(const char *__restrict__ q, size_t vstride, int nvec,
                                                  const double2 *__restrict__ z, size_t nelem,
-                                                 double *__restrict__ pproj, int ntiles)
+                                                 double *__restrict__ pproj, int ntiles, const Scalars *sc,
+                                                 int second)
 {
+    static_assert(kDotVecs == 16, "a wave sums 32 values");
+    if (second && !sc->again) return;
     __shared__ double red[kWaves][2 * kDotVecs];
     const int t = blockIdx.x, j0 = blockIdx.y * kDotVecs;
     const int nj = min(kDotVecs, nvec - j0);
-    double re[kDotVecs], im[kDotVecs];
+    double h[2 * kDotVecs];  // re, im per vector
 #pragma unroll
-    for (int jj = 0; jj < kDotVecs; ++jj) re[jj] = im[jj] = 0.0;
+    for (int jj = 0; jj < 2 * kDotVecs; ++jj) h[jj] = 0.0;
     for (size_t e = (size_t)t * kBlock + threadIdx.x; e < nelem; e += (size_t)ntiles * kBlock) {
         const double2 zv = z[e];
         // every load unconditional (a short last chunk re-reads its last
@@ -63,19 +154,13 @@ __global__ __launch_bounds__(kBlock) void k_proj(const char *__restrict__ q, siz
 #pragma unroll
         for (int jj = 0; jj < kDotVecs; ++jj) {
             const double2 qv = qvec(q, vstride, j0 + min(jj, nj - 1))[e];
-            re[jj] += qv.x * zv.x + qv.y * zv.y;
-            im[jj] += qv.x * zv.y - qv.y * zv.x;
+            h[2 * jj] += qv.x * zv.x + qv.y * zv.y;
+            h[2 * jj + 1] += qv.x * zv.y - qv.y * zv.x;
         }
     }
-    wave_sum(re);
-    wave_sum(im);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0)
-#pragma unroll
-        for (int jj = 0; jj < kDotVecs; ++jj) {
-            red[w][2 * jj] = re[jj];
-            red[w][2 * jj + 1] = im[jj];
-        }
+    const double sum = wave_sum_spread<16, 32>(h);
+    if ((lane & 1) == 0) red[w][lane >> 1] = sum;
     __syncthreads();
     if (threadIdx.x < 2 * nj) {
         double a = red[0][threadIdx.x];
@@ -86,8 +171,10 @@ __global__ __launch_bounds__(kBlock) void k_proj(const char *__restrict__ q, siz
 }
 
 // h_j = sum of the ntiles partials of vector j (workgroup j; fixed order).
-__global__ __launch_bounds__(kBlock) void k_proj_fold(const double *__restrict__ pproj, int ntiles, double *h)
+__global__ __launch_bounds__(kBlock) void k_proj_fold(const double *__restrict__ pproj, int ntiles, double *h,
+                                                      const Scalars *sc, int second)
 {
+    if (second && !sc->again) return;
     __shared__ double red[kWaves][2];
     const int j = blockIdx.x;
     double s[2] = {0.0, 0.0};
@@ -109,19 +196,45 @@ __global__ __launch_bounds__(kBlock) void k_proj_fold(const double *__restrict__
     }
 }
 
-// z -= sum_j h_j q_j.  The loop over element tiles has a workgroup-uniform
+// Scalar update of iteration i from ||z||^2 (alpha_i is there): beta_i = ||z||, the
+// running scale max(|alpha_j|, beta_{j-1}) and the breakdown test beta_i <= 1e-13
+// scale, which stops the recurrence with k_eff = i (the Krylov space is
+// invariant).
+__device__ __forceinline__ void norm_update(double zz, int i, const double *alpha, double *beta, Scalars *sc)
+{
+    if (sc->kstop < i) return;
+    const double al = alpha[i];
+    const double b = sqrt(zz);
+    if (!isfinite(b) || !isfinite(al)) {
+        sc->status = 3;
+        sc->kstop = -1;
+        return;
+    }
+    beta[i] = b;
+    double scale = fmax(sc->scale, fabs(al));
+    if (i > 1) scale = fmax(scale, beta[i - 1]);
+    sc->scale = scale;
+    sc->keff = i;
+    if (b <= 1e-13 * scale) sc->kstop = i;
+}
+
+// z -= sum_j h_j q_j and ||z||^2; the last workgroup decides whether a second pass
+// follows, else updates the scalars of iteration i = nvec.  The loop over element tiles has a workgroup-uniform
 // trip count (the LDS staging of h needs every thread at the barriers).
 __global__ __launch_bounds__(kBlock) void k_sub_q(const char *__restrict__ q, size_t vstride, int nvec,
                                                   const double *__restrict__ h, double2 *__restrict__ z,
-                                                  size_t nelem)
+                                                  size_t nelem, const double *alpha, double *beta, Scalars *sc,
+                                                  double *partials, int second)
 {
+    if (second && !sc->again) return;
     __shared__ double hs[2 * kSubChunk];
+    double zz[1] = {0.0};
     const size_t step = (size_t)gridDim.x * kBlock;
     for (size_t base = (size_t)blockIdx.x * kBlock; base < nelem; base += step) {
         const size_t e = base + threadIdx.x;
         const bool live = e < nelem;
         double ar = 0.0, ai = 0.0;
-        for (int j0 = 0; j0 < nvec; j0 += kSubChunk) {
+        for (int j0 = (nvec - 1) / kSubChunk * kSubChunk; j0 >= 0; j0 -= kSubChunk) {
             const int nj = min(kSubChunk, nvec - j0);
             // coefficients padded with zeros to whole groups of kDotVecs, so
             // each group issues all its loads before the first use
@@ -130,7 +243,7 @@ __global__ __launch_bounds__(kBlock) void k_sub_q(const char *__restrict__ q, si
             for (int i = threadIdx.x; i < 2 * njp; i += kBlock) hs[i] = i < 2 * nj ? h[2 * (size_t)j0 + i] : 0.0;
             __syncthreads();
             if (live) {
-                for (int jb = 0; jb < njp; jb += kDotVecs) {
+                for (int jb = njp - kDotVecs; jb >= 0; jb -= kDotVecs) {
                     double2 qv[kDotVecs];
 #pragma unroll
                     for (int u = 0; u < kDotVecs; ++u) qv[u] = qvec(q, vstride, j0 + min(jb + u, nj - 1))[e];
@@ -145,10 +258,27 @@ __global__ __launch_bounds__(kBlock) void k_sub_q(const char *__restrict__ q, si
             }
         }
         if (live) {
-            const double2 zv = z[e];
-            z[e] = make_double2(zv.x - ar, zv.y - ai);
+            double2 zv = z[e];
+            zv.x -= ar;
+            zv.y -= ai;
+            z[e] = zv;
+            zz[0] += zv.x * zv.x + zv.y * zv.y;
         }
     }
+    double tot[1];
+    if (!grid_reduce(zz, partials, &sc->ticket, tot)) return;
+    double hh = 0.0;
+    if (!second) {
+        double s[1] = {0.0};
+        for (int j = threadIdx.x; j < 2 * nvec; j += kBlock) s[0] += h[j] * h[j];
+        __shared__ double red[kWaves][1];
+        double b[1];
+        block_partial(s, red, b);
+        hh = b[0];
+    }
+    if (threadIdx.x != 0) return;
+    sc->again = !second && hh > kAgain * kAgain * tot[0];
+    if (!sc->again) norm_update(tot[0], nvec, alpha, beta, sc);
 }
 
 // beta_0 = ||psi|| (grid-wide fixed-order reduction); kstop = 0 for psi = 0,
@@ -190,38 +320,6 @@ __global__ __launch_bounds__(kBlock) void k_scale_q(const double2 *__restrict__ 
     }
 }
 
-// Scalar update of iteration i from ||z||^2: alpha_i = Re h1_i (first
-// projection pass), beta_i = ||z||, the running scale max(|alpha_j|,
-// beta_{j-1}) and the breakdown test beta_i <= 1e-13 scale, which stops the
-// recurrence with k_eff = i (the Krylov space is invariant).
-__global__ __launch_bounds__(kBlock) void k_norm_update(const double2 *__restrict__ z, size_t nelem,
-                                                        const double *__restrict__ h1, int i, double *alpha,
-                                                        double *beta, Scalars *sc, double *partials)
-{
-    double s[1] = {0.0};
-    for (size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x; e < nelem; e += (size_t)gridDim.x * kBlock) {
-        const double2 v = z[e];
-        s[0] += v.x * v.x + v.y * v.y;
-    }
-    double tot[1];
-    if (!grid_reduce(s, partials, &sc->ticket, tot)) return;
-    if (threadIdx.x != 0 || sc->kstop < i) return;
-    const double al = h1[2 * (i - 1)];
-    const double b = sqrt(tot[0]);
-    if (!isfinite(b) || !isfinite(al)) {
-        sc->status = 3;
-        sc->kstop = -1;
-        return;
-    }
-    alpha[i] = al;
-    beta[i] = b;
-    double scale = fmax(sc->scale, fabs(al));
-    if (i > 1) scale = fmax(scale, beta[i - 1]);
-    sc->scale = scale;
-    sc->keff = i;
-    if (b <= 1e-13 * scale) sc->kstop = i;
-}
-
 // Y[:, v] = sum_j t[j][v] q_j for v < r: the basis is streamed once for up to
 // kRitzVecs vectors; rows of t are staged in LDS.
 __global__ __launch_bounds__(kBlock) void k_ritz(const char *__restrict__ q, size_t vstride, int nvec,
@@ -261,20 +359,26 @@ __global__ __launch_bounds__(kBlock) void k_ritz(const char *__restrict__ q, siz
 
 }  // namespace
 
-void launch_proj(const char *q, size_t vstride, int nvec, const double2 *z, size_t nelem, double *pproj,
-                 double *h, hipStream_t st)
+void launch_lanczos_local(const Op &op, const double2 *q, const double2 *qm, double2 *w, int i, double *alpha,
+                          const double *beta, const Scalars *sc, double *partials, int nblocks, hipStream_t st)
 {
-    const int nchunk = (nvec + kDotVecs - 1) / kDotVecs;
-    const int ntiles = std::max(1, std::min(proj_tiles(nelem), kProjWorkgroups / nchunk));
-    hipLaunchKernelGGL(k_proj, dim3(ntiles, nchunk), dim3(kBlock), 0, st, q, vstride, nvec, z, nelem, pproj,
-                       ntiles);
-    hipLaunchKernelGGL(k_proj_fold, dim3(nvec), dim3(kBlock), 0, st, pproj, ntiles, h);
+    const size_t sites = (size_t)op.nx * op.ny;
+    const int na = (int)std::min<size_t>((sites + kBlock - 1) / kBlock, nblocks);
+    hipLaunchKernelGGL(k_eig_apply, dim3(na), dim3(kBlock), 0, st, op, q, w, partials);
+    hipLaunchKernelGGL(k_local, dim3(nblocks), dim3(kBlock), 0, st, q, qm, w, 2 * sites, i, alpha, beta, sc, partials, na);
 }
 
-void launch_sub_q(const char *q, size_t vstride, int nvec, const double *h, double2 *z, size_t nelem, int nblocks,
-                  hipStream_t st)
+void launch_orth(const char *q, size_t vstride, int nvec, double2 *z, size_t nelem, double *pproj, double *h,
+                 const double *alpha, double *beta, Scalars *sc, double *partials, int nblocks, bool second,
+                 hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sub_q, dim3(nblocks), dim3(kBlock), 0, st, q, vstride, nvec, h, z, nelem);
+    const int nchunk = (nvec + kDotVecs - 1) / kDotVecs;
+    const int ntiles = std::max(1, std::min(proj_tiles(nelem), (second ? kProjSecond : kProjWorkgroups) / nchunk));
+    hipLaunchKernelGGL(k_proj, dim3(ntiles, nchunk), dim3(kBlock), 0, st, q, vstride, nvec, z, nelem, pproj, ntiles,
+                       sc, (int)second);
+    hipLaunchKernelGGL(k_proj_fold, dim3(nvec), dim3(kBlock), 0, st, pproj, ntiles, h, sc, (int)second);
+    hipLaunchKernelGGL(k_sub_q, dim3(second ? std::min(nblocks, kProjSecond) : nblocks), dim3(kBlock), 0, st, q, vstride,
+                       nvec, h, z, nelem, alpha, beta, sc, partials, (int)second);
 }
 
 void launch_first_q(const double2 *psi, size_t nelem, double2 *q1, Scalars *sc, double *beta, double *partials,
@@ -284,12 +388,10 @@ void launch_first_q(const double2 *psi, size_t nelem, double2 *q1, Scalars *sc, 
     hipLaunchKernelGGL(k_scale_q, dim3(nblocks), dim3(kBlock), 0, st, psi, nelem, q1, beta, 0, sc);
 }
 
-void launch_norm_next(const double2 *z, size_t nelem, const double *h1, int i, int k, double *alpha, double *beta,
-                      Scalars *sc, double *partials, double2 *qn, int nblocks, hipStream_t st)
+void launch_next_q(const double2 *z, size_t nelem, int i, const double *beta, const Scalars *sc, double2 *qn,
+                   int nblocks, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_norm_update, dim3(nblocks), dim3(kBlock), 0, st, z, nelem, h1, i, alpha, beta, sc,
-                       partials);
-    if (i < k) hipLaunchKernelGGL(k_scale_q, dim3(nblocks), dim3(kBlock), 0, st, z, nelem, qn, beta, i, sc);
+    hipLaunchKernelGGL(k_scale_q, dim3(nblocks), dim3(kBlock), 0, st, z, nelem, qn, beta, i, sc);
 }
 
 void launch_ritz(const char *q, size_t vstride, int nvec, const double *t, int r, double2 *y, size_t nelem,

@@ -258,3 +258,30 @@ def test_eigen_early_stop(torch_cuda, Prop):
     assert len(ev2) == 2 and np.all(bd2 <= tol)
     for e in ev2:
         assert np.min(np.abs(res[8][0] - e)) <= 1e-7
+
+
+# a projection covers 16 vectors a workgroup and the update 256 coefficients a
+# chunk; 9 x 7: one partly filled tile, 61 x 50: the elements end inside a tile
+@pytest.mark.parametrize("nx,ny,bc", [(9, 7, 0), (61, 50, 1)])
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 33, 126, 257, 289])
+def test_orthonormal_at_chunk_edges(torch_cuda, Prop, nx, ny, bc, k):
+    """Every Ritz value of T_k with its vector (tol large enough to take all):
+    unit vectors, orthogonal to rounding, with the residual of their bound."""
+    torch = torch_cuda
+    if k > 2 * nx * ny:
+        pytest.skip("more iterations than states")
+    prob = prob_of(nx, ny, bc=bc)
+    psi0 = packets.random_spinor(prob, 5)
+    say(f"eigen reorth chunk edges {nx}x{ny} k={k}")
+    # clusters closer than tol would merge, so tol only spans the largest bound
+    prop = Prop(prob, 1, "fp64", k_eigen=k, reorth=True)
+    H = hz.dense_h(prob)
+    norm = float(abs(H).sum(axis=1).max())
+    ev, bd, Y = prop.eigen_vectors(torch.from_numpy(psi0).cuda(), k, -1e9, 1e9, 1e-3 * norm, n_wanted=k)
+    prop.close()
+    M = Y.cpu().numpy().reshape(len(ev), psi0.size)  # (no value of a short T may have converged)
+    # k vectors, each projection rounded to a few eps
+    assert np.allclose(M.conj() @ M.T, np.eye(len(ev)), atol=64 * k * 2.0 ** -52)
+    for th, y in zip(ev, M):
+        # a cluster's mean is within tol of each member, whose bound is at most tol
+        assert np.linalg.norm(H @ y - th * y) <= 2.0 * k * 1e-3 * norm
