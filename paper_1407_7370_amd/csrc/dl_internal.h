@@ -173,9 +173,19 @@ struct ResidentTiles {
         return tile > scratch ? tile : scratch;
     }
 };
+// Iterations p0 .. p1 of the eigen mode's recurrence: u_1 is the start vector (two
+// planes), later vectors hold the components of a site side by side; u2 and o2
+// are u_{p0-2} (not read for p0 = 2) and u_{p1-1}, and o1, o2 may be u1, u2.
+struct ResidentEigen {
+    int p0, p1;
+    const double2 *u1, *u2;
+    double2 *o1, *o2;
+    double *alpha, *gamma;
+};
 struct ResidentArgs {
     Op op;
     ResidentTiles t;
+    ResidentEigen eig;  // launch_resident_eigen only
     int m, n_steps;
     double2 *psi[2];           // step s reads psi[s & 1] and writes psi[(s + 1) & 1], or,
     size_t state_stride;       // when not 0, reads and writes states s and s + 1 of that byte stride from psi[0]
@@ -203,6 +213,8 @@ struct ResidentArgs {
 ResidentTiles resident_tiles(int nx, int ny, int wgs);
 // Cooperative launch of n_steps <= kResidentSteps steps (any error: nothing ran).
 hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st);
+// Cooperative launch of a.eig's iterations (op, t, sc, red, halo, epoch and eig of a).
+hipError_t launch_resident_eigen(const ResidentArgs &a, hipStream_t st);
 void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *stats, int first, int n, double reps,
                             double rabs, hipStream_t st);
 // Exchange buffers, epoch and ticks to zero (a new workspace, or after a timeout).
@@ -402,6 +414,17 @@ constexpr int kHermRitzLen = 2 + 2 * kHermRitzMax;
 constexpr int kHermRitzK = 2048;
 void launch_herm_ritz(const HermRun *runs, const double *windows, int n, int k_max, int every, int ncheck, double *out,
                       hipStream_t st);
+
+// Ritz values of T_k (diagonal alpha[0..k), off-diagonal beta[0..k-1)) in (lo, hi],
+// unless the recurrence has ended (sc->kstop <= k): their number into out[0] (-1:
+// more than kRitzMax), the values ascending into out[1 ..] and the last component
+// of their unit eigenvectors into out[1 + kRitzMax ..], beta[k-1] into the last
+// double.  k <= kRitzK.
+constexpr int kRitzMax = 64;
+constexpr int kRitzLen = 2 + 2 * kRitzMax;
+constexpr int kRitzK = 4096;
+hipError_t launch_ritz_window(const double *alpha, const double *beta, int k, double lo, double hi, const Scalars *sc,
+                              double *out, hipStream_t st);
 
 // Eigen mode with full reorthogonalisation (eigen_kernels.hip).  Stored
 // complex128 vectors q_1..q_K at q + (j-1) * vstride; the projection partial

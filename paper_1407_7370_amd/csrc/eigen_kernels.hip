@@ -320,6 +320,199 @@ __global__ __launch_bounds__(kBlock) void k_scale_q(const double2 *__restrict__ 
     }
 }
 
+// Ritz values of T_k in (lo, hi], one workgroup per value (blockIdx.x): Sturm
+// counts of kBlock shifts at a time, so that a pass gains eight bits, and the last
+// component of the unit eigenvector z from the twisted factorisation of T - theta
+// (Parlett and Dhillon, Linear Algebra Appl. 267 (1997) 247): pivots p_i from the
+// top, m_i from the bottom, the twist r where |p_r + m_r - (d_r - theta)| is smallest;
+// z_r = 1, (z_i / z_{i+1})^2 = e_i^2 / p_i^2 above it and (z_{i+1} / z_i)^2 = e_i^2 /
+// m_{i+1}^2 below.
+// A count is the sign changes of the leading minors, f_i = (d_i - x) f_{i-1} -
+// e_{i-1}^2 f_{i-2} with T scaled by a power of two to norm <= 1 and both minors
+// rescaled every kRows rows: four instructions a row and no division (the pivots'
+// recurrence waits about 60 cycles a row for its reciprocal).
+// Bound: the chain of rows, 141 us a checkpoint on average to k = 1600, against
+// 1.5 ms on the host, which was longer than the 64 iterations (0.68 ms at 1024^2)
+// that it ran beside.
+__global__ __launch_bounds__(kBlock) void k_ritz_window(const double *__restrict__ alpha,
+                                                        const double *__restrict__ beta, int k, double lo, double hi,
+                                                        const Scalars *sc, double *out)
+{
+    constexpr int kRows = 16;
+    extern __shared__ double2 td[];  // (d_i, e_i^2) of the scaled matrix, then the pivots
+    double *const top = reinterpret_cast<double *>(td + k), *const bot = top + k;
+    __shared__ double red[kWaves];
+    __shared__ int cnt[kWaves];
+    __shared__ double res[4];
+    const int t = (int)threadIdx.x, lane = t & 63, w = t >> 6;
+    if (sc->kstop <= k) return;  // the recurrence has ended: the host solves its last T
+    // power of two that takes the norm to at most 1
+    double tn = 0.0;
+    for (int i = t; i < k; i += kBlock) {
+        const double l = i > 0 ? fabs(beta[i - 1]) : 0.0, r = i + 1 < k ? fabs(beta[i]) : 0.0;
+        tn = fmax(tn, fabs(alpha[i]) + l + r);
+    }
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) tn = fmax(tn, __shfl_xor(tn, s, 64));
+    if (lane == 0) red[w] = tn;
+    __syncthreads();
+    for (int i = 0; i < kWaves; ++i) tn = fmax(tn, red[i]);
+    const int ex = tn > 0.0 ? ilogb(tn) + 1 : 0;
+    for (int i = t; i < k; i += kBlock) {
+        const double e = i + 1 < k ? ldexp(beta[i], -ex) : 0.0;
+        td[i] = make_double2(ldexp(alpha[i], -ex), e * e);
+    }
+    __syncthreads();
+    // eigenvalues at or below x
+    auto count = [&](double x) {
+        double f1 = 0.0, f = 1.0, e2 = 0.0;
+        int n = 0, i = 0;
+        uint32_t sign = 0;  // of f
+        auto row = [&](uint32_t &bits) {
+            const double2 r = td[i++];
+            const double g = fma(r.x - x, f, -(e2 * f1));
+            f1 = f;
+            f = g;
+            e2 = r.y;
+            bits = (bits << 1) | ((uint32_t)__double2hiint(f) >> 31);
+        };
+        while (i + kRows <= k) {
+            uint32_t bits = sign;
+#pragma unroll
+            for (int j = 0; j < kRows; ++j) row(bits);
+            n += __popc((bits ^ (bits >> 1)) & ((1u << kRows) - 1u));
+            sign = bits & 1u;
+            const int sh = -ilogb(fmax(fmax(fabs(f), fabs(f1)), 1e-290));
+            f = ldexp(f, sh);
+            f1 = ldexp(f1, sh);
+        }
+        while (i < k) {
+            uint32_t bits = sign;
+            row(bits);
+            n += (int)((bits ^ (bits >> 1)) & 1u);
+            sign = bits & 1u;
+        }
+        // a zero minor changes sign once with the next; a last one is negative
+        if (f == 0.0) n += (f1 < 0.0) == (sign != 0u);
+        return n;
+    };
+    // x within the wave's reach of every thread: how many of the shifts have a
+    // count of at most `target`
+    auto below = [&](double x, int target) {
+        const int c = __popcll(__ballot(count(x) <= target));
+        __syncthreads();
+        if (lane == 0) cnt[w] = c;
+        __syncthreads();
+        int s = 0;
+        for (int i = 0; i < kWaves; ++i) s += cnt[i];
+        return s;
+    };
+    const double slo = ldexp(lo, -ex), shi = ldexp(hi, -ex);
+    if (w == 0) {
+        const int c = count(lane == 0 ? slo : shi);
+        if (lane < 2) cnt[lane] = c;
+    }
+    __syncthreads();
+    const int clo = cnt[0], nw = cnt[1] - clo, v = (int)blockIdx.x;
+    if (v == 0 && t == 0) {
+        out[0] = nw > kRitzMax ? -1.0 : (double)max(nw, 0);
+        out[kRitzLen - 1] = beta[k - 1];
+    }
+    if (nw > kRitzMax || v >= nw) return;
+    double a = slo, b = shi;  // the value lies in (a, b]
+    for (int pass = 0; pass < 200; ++pass) {
+        const double mid = 0.5 * (a + b);
+        if (b - a <= 4.440892098500626e-16 * fmax(fabs(a), fabs(b)) + 1e-290 || mid <= a || mid >= b) break;
+        auto point = [&](int i) { return fmin(fmax(a + (b - a) * ((double)(i + 1) / (double)(kBlock + 1)), a), b); };
+        const int f = below(point(t), clo + v);
+        const double na = f > 0 ? point(f - 1) : a, nb = f < kBlock ? point(f) : b;
+        a = na;
+        b = nb;
+    }
+    const double theta = 0.5 * (a + b);
+    // pivots: negligible ones taken as negative
+    auto keep = [](double q) { return fabs(q) < 1e-280 ? -1e-280 : q; };
+    auto recip = [](double q) {
+        double r = __builtin_amdgcn_rcp(q);
+        r = fma(r, fma(-q, r, 1.0), r);
+        return fma(r, fma(-q, r, 1.0), r);
+    };
+    if (w == 0) {
+        double q = 1.0, e2 = 0.0;
+#pragma unroll 8
+        for (int i = 0; i < k; ++i) {
+            const double2 r = td[i];
+            q = keep((r.x - theta) - e2 * recip(q));
+            e2 = r.y;
+            if (lane == 0) top[i] = q;
+        }
+    } else if (w == 1) {
+        double q = 1.0;
+#pragma unroll 8
+        for (int i = k - 1; i >= 0; --i) {
+            const double2 r = td[i];
+            q = keep((r.x - theta) - r.y * recip(q));
+            if (lane == 0) bot[i] = q;
+        }
+    }
+    __syncthreads();
+    double best = INFINITY;
+    int twist = k;
+    for (int i = t; i < k; i += kBlock) {
+        const double g = fabs(top[i] + bot[i] - (td[i].x - theta));
+        if (g < best) {
+            best = g;
+            twist = i;
+        }
+    }
+    auto better = [&](double g, int i) {
+        if (g < best || (g == best && i < twist)) {
+            best = g;
+            twist = i;
+        }
+    };
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) better(__shfl_xor(best, s, 64), __shfl_xor(twist, s, 64));
+    if (lane == 0) {
+        red[w] = best;
+        cnt[w] = twist;
+    }
+    __syncthreads();
+    for (int i = 0; i < kWaves; ++i) better(red[i], cnt[i]);
+    if (twist >= k) twist = k - 1;  // (non-finite chain: the call fails on its scalars)
+    // squared ratios of neighbouring components, away from the twist
+    for (int i = t; i < k; i += kBlock) {
+        if (i < twist) {
+            const double r = recip(top[i]);
+            top[i] = td[i].y * r * r;
+        } else if (i > twist) {
+            const double r = recip(bot[i]);
+            bot[i] = td[i - 1].y * r * r;
+        }
+    }
+    __syncthreads();
+    if (t == 0) {
+        double s = 0.0;
+#pragma unroll 8
+        for (int i = 0; i < twist; ++i) s = top[i] * (1.0 + s);
+        res[0] = s;
+    } else if (t == 64) {
+        double s = 0.0, last = 1.0;
+#pragma unroll 8
+        for (int i = k - 1; i > twist; --i) {
+            s = bot[i] * (1.0 + s);
+            last *= bot[i];
+        }
+        res[1] = s;
+        res[2] = last;
+    }
+    __syncthreads();
+    if (t == 0) {
+        out[1 + v] = ldexp(theta, ex);
+        out[1 + kRitzMax + v] = sqrt(res[2] / (1.0 + res[0] + res[1]));
+    }
+}
+
 // Y[:, v] = sum_j t[j][v] q_j for v < r: the basis is streamed once for up to
 // kRitzVecs vectors; rows of t are staged in LDS.
 __global__ __launch_bounds__(kBlock) void k_ritz(const char *__restrict__ q, size_t vstride, int nvec,
@@ -386,6 +579,17 @@ void launch_first_q(const double2 *psi, size_t nelem, double2 *q1, Scalars *sc, 
 {
     hipLaunchKernelGGL(k_first_norm, dim3(nblocks), dim3(kBlock), 0, st, psi, nelem, sc, beta, partials);
     hipLaunchKernelGGL(k_scale_q, dim3(nblocks), dim3(kBlock), 0, st, psi, nelem, q1, beta, 0, sc);
+}
+
+hipError_t launch_ritz_window(const double *alpha, const double *beta, int k, double lo, double hi, const Scalars *sc,
+                              double *out, hipStream_t st)
+{
+    const size_t lds = 32 * (size_t)k;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_ritz_window),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ritz_window, dim3(kRitzMax), dim3(kBlock), lds, st, alpha, beta, k, lo, hi, sc, out);
+    return hipGetLastError();
 }
 
 void launch_next_q(const double2 *z, size_t nelem, int i, const double *beta, const Scalars *sc, double2 *qn,

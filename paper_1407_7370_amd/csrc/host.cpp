@@ -827,14 +827,50 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
     const int K1 = k_max + 1;  // the extra iteration yields beta_k for the bounds
     dl::launch_first(op, t1, v[1], fields, alpha, gamma, sc, partials, K1, 0, st);
     std::vector<double> ha(K1 + 1), hg(K1 + 1);
-    dl::Scalars hs;
-    auto fetch = [&]() -> dl_status {
-        DL_HIP(ctx, hipMemcpyAsync(ha.data(), alpha, sizeof(double) * (K1 + 1), hipMemcpyDeviceToHost, st));
-        DL_HIP(ctx, hipMemcpyAsync(hg.data(), gamma, sizeof(double) * (K1 + 1), hipMemcpyDeviceToHost, st));
-        DL_HIP(ctx, hipMemcpyAsync(&hs, sc, sizeof(hs), hipMemcpyDeviceToHost, st));
+    // scalars and (behind them) the device's Ritz values of a checkpoint; the chain
+    struct {
+        dl::Scalars sc;
+        char pad[align256(sizeof(dl::Scalars)) - sizeof(dl::Scalars)];
+        double ritz[dl::kRitzLen];
+    } rec;
+    static_assert(dl::kRitzLen <= dl::kChainLen * dl::kResidentSteps, "the steps' chains hold the record");
+    const dl::Scalars &hs = rec.sc;
+    double *const d_ritz = reinterpret_cast<double *>(ws + E.chain);
+    auto fetch = [&](bool chain) -> dl_status {
+        if (chain) {
+            DL_HIP(ctx, hipMemcpyAsync(ha.data(), alpha, sizeof(double) * (K1 + 1), hipMemcpyDeviceToHost, st));
+            DL_HIP(ctx, hipMemcpyAsync(hg.data(), gamma, sizeof(double) * (K1 + 1), hipMemcpyDeviceToHost, st));
+        }
+        DL_HIP(ctx, hipMemcpyAsync(&rec, sc, sizeof(rec), hipMemcpyDeviceToHost, st));
         DL_HIP(ctx, hipStreamSynchronize(st));
-        if (hs.status != 0) return ctx->fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction in eigen mode");
+        if (hs.status == dl::kStatusTimeout) clear_failure(ctx, hs.status);
+        if (hs.status != 0) return ctx->status_fail(hs.status, "in eigen mode");
         return DL_OK;
+    };
+    // grids that fit the chip run the passes up to a checkpoint in one launch
+    // (1024^2 with potential and field: 25.2 us a pass as sweeps, 10.7 us so)
+    dl::ResidentArgs ra{};
+    ra.op = op;
+    ra.sc = sc;
+    ra.red = reinterpret_cast<unsigned long long *>(ws + E.comm);
+    ra.halo = reinterpret_cast<unsigned long long *>(ws + E.comm + dl::kCommRed);
+    ra.epoch = &sc->epoch;
+    ra.eig.alpha = alpha;
+    ra.eig.gamma = gamma;
+    auto resident = [&](int p0, int p1) {
+        if (ctx->resident.rows == 0) return false;
+        ra.t = ctx->resident;
+        ra.eig.p0 = p0;
+        ra.eig.p1 = p1;
+        ra.eig.u1 = v[(p0 - 1) % 3];
+        ra.eig.u2 = v[(p0 + 1) % 3];
+        ra.eig.o1 = v[p1 % 3];
+        ra.eig.o2 = v[(p1 - 1) % 3];
+        if (dl::launch_resident_eigen(ra, st) == hipSuccess) return true;
+        // not available on this device: sweeps from here on
+        (void)hipGetLastError();
+        ctx->resident = dl::ResidentTiles{};
+        return false;
     };
     // T_k after pass p: alpha_1..alpha_k in ha[1..], beta_1..beta_k in hg[2..]
     // (gamma_{j+1} = beta_j), so k = p - 1 is complete after pass p.  Converged
@@ -849,41 +885,65 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
     };
     int pending = 0;  // checkpoint fetched but not yet solved
     for (int pp = 2; pp <= K1; ++pp) {
-        dl::PassArgs a{};
-        a.op = op;
-        a.t = tp[pp == 2 ? 0 : (pp == 3 ? 1 : 2)];
-        a.u1 = v[(pp - 1) % 3];
-        a.u2 = pp >= 3 ? v[(pp - 2) % 3] : nullptr;
-        a.uo = v[pp % 3];
-        a.field = fields;
-        a.alpha = alpha;
-        a.gamma = gamma;
-        a.sc = sc;
-        a.partials = partials;
-        a.pass = pp;
-        a.m = K1;
-        dl::launch_recur(a, false, st);
+        const int next = std::min(K1, (pp - 2) / kEigenCheckEvery * kEigenCheckEvery + kEigenCheckEvery + 1);
+        if ((pp - 2) % kEigenCheckEvery == 0 && resident(pp, next)) {
+            pp = next;
+        } else {
+            dl::PassArgs a{};
+            a.op = op;
+            a.t = tp[pp == 2 ? 0 : (pp == 3 ? 1 : 2)];
+            a.u1 = v[(pp - 1) % 3];
+            a.u2 = pp >= 3 ? v[(pp - 2) % 3] : nullptr;
+            a.uo = v[pp % 3];
+            a.field = fields;
+            a.alpha = alpha;
+            a.gamma = gamma;
+            a.sc = sc;
+            a.partials = partials;
+            a.pass = pp;
+            a.m = K1;
+            dl::launch_recur(a, false, st);
+        }
         if ((pp - 1) % kEigenCheckEvery == 0 && pp < K1) {
             DL_HIP(ctx, hipGetLastError());
-            // the previous checkpoint is solved while the device runs the
-            // passes since then; the decision to stop is the same, only the
+            // windows of up to kRitzMax values are solved on the device
+            const int k = pp - 1;
+            const bool on_device = k <= dl::kRitzK && std::isfinite(e_lo) && std::isfinite(e_hi);
+            if (on_device) DL_HIP(ctx, dl::launch_ritz_window(alpha + 1, gamma + 2, k, e_lo, e_hi, sc, d_ritz, st));
+            // others here: the previous checkpoint is solved while the device runs
+            // the passes since then; the decision to stop is the same, only the
             // passes queued meanwhile are extra work
             if (pending > 0) {
                 harvest(pending);
                 pending = 0;
-                if ((int)found.size() >= n_wanted) break;
             }
-            const dl_status s = fetch();
+            const bool enough = (int)found.size() >= n_wanted;
+            dl_status s = fetch(!on_device && !enough);
             if (s != DL_OK) return s;
+            if (enough) break;
             if (hs.kstop < pp) break;  // breakdown: the recurrence is over
-            pending = pp - 1;
+            const int nw = on_device ? (int)rec.ritz[0] : -1;
+            if (nw >= 0) {
+                const double *r = rec.ritz + 1;
+                const std::vector<double> lam(r, r + nw), zl(r + dl::kRitzMax, r + dl::kRitzMax + nw);
+                const int nf = ritz_select(lam, zl, rec.ritz[dl::kRitzLen - 1], e_lo, e_hi, tol, (int)ev.size(), ev.data(),
+                                           bd.data(), nullptr);
+                merge_converged(found, ev.data(), bd.data(), nf, tol);
+                if ((int)found.size() >= n_wanted) break;
+            } else {
+                if (on_device) {
+                    s = fetch(true);
+                    if (s != DL_OK) return s;
+                }
+                pending = k;
+            }
         }
     }
     DL_HIP(ctx, hipGetLastError());
-    const dl_status s = fetch();
-    if (s != DL_OK) return s;
     if (pending > 0) harvest(pending);
     if ((int)found.size() < n_wanted) {
+        const dl_status s = fetch(true);
+        if (s != DL_OK) return s;
         const int k = std::min(hs.keff, k_max);
         if (k > 0) harvest(k);
     }

@@ -195,13 +195,18 @@ __device__ __forceinline__ void opaque(X &x)
     asm volatile("" : "+v"(x));
 }
 
-template <class TO, int K, int TERMS>
+// EIG: iterations p0 .. p1 of the plain recurrence of the eigen mode in place of
+// time steps (ResidentEigen): no basis, no exponential; u_{p0-1} and u_{p0-2} are
+// read from memory first and u_{p1}, u_{p1-1} written last.
+template <class TO, int K, int TERMS, bool EIG>
 __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 {
     double2 *const tile = resident_tile;
     ResidentShared &sh = shared_state();
     Scalars *sc = a.sc;
     if (sc->status != 0) return;
+    if constexpr (EIG)
+        if (sc->kstop < a.eig.p0) return;
     constexpr int NW = kSiteWords<TO>;
     // two tile buffers (u_p is formed into the one that does not hold u_{p-1})
     // where both fit, else one, exchanged with the registers between barriers
@@ -457,9 +462,10 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
     // by other workgroups (device-coherent loads)
     const uint32_t plane = (uint32_t)op.nx * (uint32_t)op.ny * 16u;
     const uint32_t vec_bytes = (uint32_t)op.nx * (uint32_t)op.ny * (uint32_t)sizeof(Raw<TO>);
-    auto load_border = [&](const double2 *psi) {
-        const __amdgpu_buffer_rsrc_t d0 = row_rsrc(reinterpret_cast<const char *>(psi), plane);
-        const __amdgpu_buffer_rsrc_t d1 = row_rsrc(reinterpret_cast<const char *>(psi) + plane, plane);
+    // (paired: the components of a site side by side, else two planes)
+    auto load_border = [&](const double2 *psi, bool paired) {
+        const uint32_t stride = paired ? 32u : 16u, off1 = paired ? 16u : plane;
+        const __amdgpu_buffer_rsrc_t d0 = row_rsrc(reinterpret_cast<const char *>(psi), 2u * plane);
         const int n = 4 * (Tx + Ty) + 4;
         for (int e = t; e < n; e += kRBlock) {
             int i, j;
@@ -481,10 +487,10 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
             x = x < 0 ? x + op.nx : (x >= op.nx ? x - op.nx : x);
             y = y < 0 ? y + op.ny : (y >= op.ny ? y - op.ny : y);
             if (!ok) continue;  // outside a Dirichlet domain: LDS keeps its zero
-            const uint32_t off = ((uint32_t)y * (uint32_t)op.nx + (uint32_t)x) * 16u;
+            const uint32_t off = ((uint32_t)y * (uint32_t)op.nx + (uint32_t)x) * stride;
             const int s = at(i, j);
             A0[s] = ld16<double2, kPolCoherent>(d0, off);
-            A1[s] = ld16<double2, kPolCoherent>(d1, off);
+            A1[s] = ld16<double2, kPolCoherent>(d0, off + off1);
         }
     };
     // (A - shift) applied at the rows of the run from LDS: f(k, c, (A - shift) c)
@@ -507,32 +513,6 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
         };
         unroll_steps(row, std::make_integer_sequence<int, K>{});
     };
-
-    // zero the tile (sites outside a Dirichlet domain stay zero), then psi
-    for (int s = t; s < tile_words; s += kRBlock) tile[s] = make_double2(0.0, 0.0);
-    if (t == 0) sh.dead = 0;
-    __syncthreads();
-    const double2 *in = a.state_in(0);
-    {
-        const size_t sites = (size_t)op.nx * op.ny;
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (own >> k & 1u) {
-                const size_t g = (size_t)(g0 + k * op.nx);
-                A0[s0 + k * W] = in[g];
-                A1[s0 + k * W] = in[sites + g];
-            }
-    }
-    load_border(in);
-    __syncthreads();
-
-    unsigned long long clk[5] = {0, 0, 0, 0, 0}, mark = started;
-    auto lap = [&](int cls) {
-        if (!a.ticks) return;
-        const unsigned long long now = wall_clock64();
-        clk[cls] += now - mark;
-        mark = now;
-    };
     // see opaque()
     auto fresh = [&] {
         opaque(s0);
@@ -542,7 +522,139 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
         opaque(r0);
         opaque(g0);
     };
+    // u_p = cw (A - sig) u_{p-1} - ca u_{p-1} - cb u_{p-2} from LDS and R into LDS,
+    // u_{p-1} into R; store(k, u_p) per row
+    auto advance = [&](double gxh, double gyh, double sig, double inv_g1, double ca, double cb, Sp(&R)[K],
+                       auto &&store) {
+        double2 *const B0 = kTwo ? tile + (A0 == tile ? 2 * (P + 1) : 0) : A0, *const B1 = B0 + P + 1;
+        auto keep = [&](int k, const Sp &u, const Sp &old) {
+            const int s = form >> k & 1u ? s0 + k * W : P;
+            B0[s] = make_double2(u.r0, u.i0);
+            B1[s] = make_double2(u.r1, u.i1);
+            store(k, u);
+            R[k] = old;
+        };
+        sweep_rows(gxh, gyh, sig, [&](auto kc, const Sp &c, const Sp &w) {
+            constexpr int k = decltype(kc)::value;
+            const double on = bit_one(form, k), cw = on * inv_g1, cc = on * ca, cu = on * cb;
+            Sp u;
+            u.r0 = cw * w.r0 - cc * c.r0 - cu * R[k].r0;
+            u.i0 = cw * w.i0 - cc * c.i0 - cu * R[k].i0;
+            u.r1 = cw * w.r1 - cc * c.r1 - cu * R[k].r1;
+            u.i1 = cw * w.i1 - cc * c.i1 - cu * R[k].i1;
+            u = stored_value<TO>(u);
+            if constexpr (kTwo)
+                keep(k, u, c);
+            else
+                R[k] = u;
+        });
+        if constexpr (kTwo) {
+            A0 = B0;
+            A1 = B1;
+        } else {
+            __syncthreads();
+            fresh();
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if (k % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+                keep(k, R[k], get(k == 0 ? s0 : min(s0 + k * W, s_last)));
+            }
+        }
+        __syncthreads();
+        fresh();
+    };
+
+    // zero the tile (sites outside a Dirichlet domain stay zero), then psi
+    for (int s = t; s < tile_words; s += kRBlock) tile[s] = make_double2(0.0, 0.0);
+    if (t == 0) sh.dead = 0;
+    __syncthreads();
+    const double2 *in = EIG ? a.eig.u1 : a.state_in(0);
+    const bool paired = EIG && a.eig.p0 > 2;  // u_1 is the start vector, in planes
+    {
+        const size_t sites = (size_t)op.nx * op.ny, stride = paired ? 2 : 1, off1 = paired ? 1 : sites;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (own >> k & 1u) {
+                const size_t g = (size_t)(g0 + k * op.nx) * stride;
+                A0[s0 + k * W] = in[g];
+                A1[s0 + k * W] = in[off1 + g];
+            }
+    }
+    load_border(in, paired);
+    __syncthreads();
+
+    unsigned long long clk[5] = {0, 0, 0, 0, 0}, mark = started;
+    auto lap = [&](int cls) {
+        if (!a.ticks) return;
+        const unsigned long long now = wall_clock64();
+        clk[cls] += now - mark;
+        mark = now;
+    };
     bool timeout = false;
+    if constexpr (EIG) {
+        const int p0 = a.eig.p0, p1 = a.eig.p1;
+        Sp R[K];  // u_{p-2} at the run's rows (rim included), then u_{p-1}
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            R[k] = sp_zero();
+            if (p0 > 2 && (form >> k & 1u)) {
+                const double2 *const v = a.eig.u2 + 2 * ((size_t)grow(k) * op.nx + gx);
+                R[k] = Sp{v[0].x, v[0].y, v[1].x, v[1].y};
+            }
+        }
+        double g_cur = a.eig.gamma[p0 - 1], g_prev = p0 > 2 ? a.eig.gamma[p0 - 2] : 0.0, al_cur = a.eig.alpha[p0 - 1];
+        double scale = sc->scale;
+        int p = p0;
+        for (; p <= p1; ++p) {
+            fresh();
+            advance(0.0, 0.0, 0.0, 1.0 / g_cur, al_cur * (1.0 / g_cur), p > 2 ? g_cur / g_prev : 0.0, R,
+                    [](int, const Sp &) {});
+            ++epoch;
+            if (p < p1) publish_border();
+            double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, tot[5];
+            sweep_rows(0.0, 0.0, 0.0, [&](auto kc, const Sp &c, const Sp &y) {
+                constexpr int k = decltype(kc)::value;
+                const double w = bit_one(own, k);
+                acc[0] += w * sp_norm2(c);
+                acc[1] += w * sp_redot(c, y);
+                acc[2] += w * sp_redot(c, R[k]);
+            });
+            publish_sums(acc, IC<3>{});
+            if (!collect(tot, IC<3>{}, p < p1)) {
+                timeout = true;
+                break;
+            }
+            // (never the last iteration of a step: beta_k is gamma_{k+1} here)
+            constexpr int kNoLast = 0x7fffffff;
+            const RecurTail o = recur_tail_eval(TailIn{kNoLast, g_cur, 0.0, scale, al_cur}, p, kNoLast, tot);
+            if (wg == 0 && t == 0) recur_tail_store(sc, a.eig.alpha, a.eig.gamma, p, o);
+            if (o.fail || o.breakdown) break;
+            scale = o.scale;
+            g_prev = g_cur;
+            g_cur = o.gp;
+            al_cur = o.al;
+        }
+        if (p > p1) {  // every workgroup has read its inputs: the buffers may be the same
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (own >> k & 1u) {
+                    const size_t g = 2 * (size_t)(g0 + k * op.nx);
+                    const Sp u = get(s0 + k * W);
+                    a.eig.o1[g] = make_double2(u.r0, u.i0);
+                    a.eig.o1[g + 1] = make_double2(u.r1, u.i1);
+                    a.eig.o2[g] = make_double2(R[k].r0, R[k].i0);
+                    a.eig.o2[g + 1] = make_double2(R[k].r1, R[k].i1);
+                }
+        }
+        if (wg == 0 && t == 0) {
+            if (timeout) {
+                sc->status = kStatusTimeout;
+                sc->kstop = -1;
+            }
+            *a.epoch = epoch;
+        }
+        return;
+    }
     int step = 0;
     for (; step < a.n_steps; ++step) {
         in = a.state_in(step);
@@ -593,43 +705,10 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                 const double inv_g1 = 1.0 / g_cur, ca = al_cur * inv_g1, cb = p > 2 ? g_cur / g_prev : 0.0;
                 const __amdgpu_buffer_rsrc_t ub = row_rsrc(basis + (size_t)(p - 2) * a.vstride, vec_bytes);
                 // u_p into LDS and (the tile itself) memory, u_{p-1} into the registers
-                double2 *const B0 = kTwo ? tile + (A0 == tile ? 2 * (P + 1) : 0) : A0, *const B1 = B0 + P + 1;
-                auto keep = [&](int k, const Sp &u, const Sp &old) {
-                    const int s = form >> k & 1u ? s0 + k * W : P;
-                    B0[s] = make_double2(u.r0, u.i0);
-                    B1[s] = make_double2(u.r1, u.i1);
+                advance(gxh, gyh, sig, inv_g1, ca, cb, R, [&](int k, const Sp &u) {
                     st_site(ub, own >> k & 1u ? (uint32_t)(g0 + k * op.nx) * (uint32_t)sizeof(Raw<TO>) : kOob,
                             to_raw<TO>(u));
-                    R[k] = old;
-                };
-                sweep_rows(gxh, gyh, sig, [&](auto kc, const Sp &c, const Sp &w) {
-                    constexpr int k = decltype(kc)::value;
-                    const double on = bit_one(form, k), cw = on * inv_g1, cc = on * ca, cu = on * cb;
-                    Sp u;
-                    u.r0 = cw * w.r0 - cc * c.r0 - cu * R[k].r0;
-                    u.i0 = cw * w.i0 - cc * c.i0 - cu * R[k].i0;
-                    u.r1 = cw * w.r1 - cc * c.r1 - cu * R[k].r1;
-                    u.i1 = cw * w.i1 - cc * c.i1 - cu * R[k].i1;
-                    u = stored_value<TO>(u);
-                    if constexpr (kTwo)
-                        keep(k, u, c);
-                    else
-                        R[k] = u;
                 });
-                if constexpr (kTwo) {
-                    A0 = B0;
-                    A1 = B1;
-                } else {
-                    __syncthreads();
-                    fresh();
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        if (k % 2 == 0) __builtin_amdgcn_sched_barrier(0);
-                        keep(k, R[k], get(k == 0 ? s0 : min(s0 + k * W, s_last)));
-                    }
-                }
-                __syncthreads();
-                fresh();
                 const bool last = p == a.m;
                 ++epoch;
                 if (!last) publish_border();
@@ -834,7 +913,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
         }
         if (!isfinite(tot[0])) break;
         if (wg == 0 && t == 0) sc->steps_done += 1;
-        if (step + 1 < a.n_steps) load_border(out);
+        if (step + 1 < a.n_steps) load_border(out, false);
         __syncthreads();
         lap(4);
     }
@@ -878,28 +957,24 @@ __global__ __launch_bounds__(kBlock) void k_zero_words(unsigned long long *p, si
 
 using ResidentKernel = void (*)(ResidentArgs);
 
-template <class TO, int TERMS>
+template <class TO, int TERMS, bool EIG>
 ResidentKernel pick_rows(int k)
 {
     switch (k) {
-    case 1: return k_resident<TO, 1, TERMS>;
-    case 2: return k_resident<TO, 2, TERMS>;
-    case 3: return k_resident<TO, 3, TERMS>;
-    case 4: return k_resident<TO, 4, TERMS>;
-    case 6: return k_resident<TO, 6, TERMS>;
-    case 8: return k_resident<TO, 8, TERMS>;
-    default: return k_resident<TO, 10, TERMS>;
+    case 1: return k_resident<TO, 1, TERMS, EIG>;
+    case 2: return k_resident<TO, 2, TERMS, EIG>;
+    case 3: return k_resident<TO, 3, TERMS, EIG>;
+    case 4: return k_resident<TO, 4, TERMS, EIG>;
+    case 6: return k_resident<TO, 6, TERMS, EIG>;
+    case 8: return k_resident<TO, 8, TERMS, EIG>;
+    default: return k_resident<TO, 10, TERMS, EIG>;
     }
 }
 
 }  // namespace
 
-hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st)
+static hipError_t launch_tiles(const ResidentArgs &a, ResidentKernel kernel, hipStream_t st)
 {
-    const bool terms = op_terms(a.op) != 0;
-    const ResidentKernel kernel =
-        mixed ? (terms ? pick_rows<float2, kTermPot | kTermB>(a.t.rows) : pick_rows<float2, 0>(a.t.rows))
-              : (terms ? pick_rows<double2, kTermPot | kTermB>(a.t.rows) : pick_rows<double2, 0>(a.t.rows));
     const size_t lds = a.t.lds_bytes();
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
@@ -908,6 +983,22 @@ hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st)
     void *params[] = {&args};
     return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kernel), dim3(a.t.ntx * a.t.nty), dim3(kRBlock),
                                       params, (unsigned)lds, st);
+}
+
+hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st)
+{
+    constexpr int kAll = kTermPot | kTermB;
+    const bool terms = op_terms(a.op) != 0;
+    const int k = a.t.rows;
+    return launch_tiles(a, mixed ? (terms ? pick_rows<float2, kAll, false>(k) : pick_rows<float2, 0, false>(k))
+                                 : (terms ? pick_rows<double2, kAll, false>(k) : pick_rows<double2, 0, false>(k)), st);
+}
+
+hipError_t launch_resident_eigen(const ResidentArgs &a, hipStream_t st)
+{
+    const int k = a.t.rows;
+    return launch_tiles(a, op_terms(a.op) != 0 ? pick_rows<double2, kTermPot | kTermB, true>(k) : pick_rows<double2, 0, true>(k),
+                        st);
 }
 
 void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *stats, int first, int n, double reps,
