@@ -36,10 +36,10 @@
 // What bounds it: the latency chain of an iteration (partials and border
 // through memory, workgroup barriers, the tile's arithmetic: 3.2 us at 64^2, 5.9
 // at 512^2) on small grids, FP64 arithmetic and LDS traffic of a tile and the
-// basis stores on the largest (16 us at 1024^2, of which 5 us are the stores).
-// Measured per step, as sweeps before and here: 64^2 m = 10 124 -> 48 us, 512^2
-// m = 12 161 -> 99 us, 1024^2 with potential and field m = 20 640 -> 493 us,
-// 1001 x 777 complex64 m = 13 364 -> 198 us.
+// basis stores on the largest (13 us at 1024^2, of which 3 us are the stores).
+// Measured per step, as sweeps before and here: 64^2 m = 10 124 -> 47 us, 512^2
+// m = 12 161 -> 99 us, 1024^2 with potential and field m = 20 640 -> 461 us,
+// 1001 x 777 complex64 m = 13 364 -> 184 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -81,27 +81,32 @@ __device__ __forceinline__ double join(unsigned long long lo, unsigned long long
 template <class T>
 constexpr int kSiteWords = sizeof(T) == 16 ? 8 : 4;
 
-// One site of a paired vector at a byte offset of its buffer.
+// Basis vectors that only this kernel reads are stored tile by tile, the tile's
+// rows one after the other, complex128 ones in two planes per tile: a wave reads
+// and writes whole lines and no line belongs to two workgroups (rows of the grid
+// with 32 bytes a site: 1024^2 m = 20 429 us a step, 400 so; 724^2 m = 12 151 and 142;
+// 512^2 and smaller the same).  Vectors that later kernels read (the adjoint's) are
+// laid out as the sweeps write them.
 template <class T, int POL>
-__device__ __forceinline__ Raw<T> ld_site_at(__amdgpu_buffer_rsrc_t r, uint32_t off)
+__device__ __forceinline__ Raw<T> ld_site_at(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t second)
 {
     if constexpr (sizeof(T) == 8) {
         return ld16<Raw<T>, POL>(r, off);
     } else {
         Raw<T> v;
         v.a = ld16<T, POL>(r, off);
-        v.b = ld16<T, POL>(r, off + 16u);
+        v.b = ld16<T, POL>(r, off + second);
         return v;
     }
 }
 template <class T>
-__device__ __forceinline__ void st_site(__amdgpu_buffer_rsrc_t r, uint32_t off, const Raw<T> &v)
+__device__ __forceinline__ void st_site(__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t second, const Raw<T> &v)
 {
     if constexpr (sizeof(T) == 8) {
         st16<Raw<T>, kPolDefault>(r, off, v);
     } else {
         st16<T, kPolDefault>(r, off, v.a);
-        st16<T, kPolDefault>(r, off + 16u, v.b);
+        st16<T, kPolDefault>(r, off + second, v.b);
     }
 }
 
@@ -462,6 +467,12 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
     // by other workgroups (device-coherent loads)
     const uint32_t plane = (uint32_t)op.nx * (uint32_t)op.ny * 16u;
     const uint32_t vec_bytes = (uint32_t)op.nx * (uint32_t)op.ny * (uint32_t)sizeof(Raw<TO>);
+    // in a basis vector: byte offset of the run's first row, strides of rows and
+    // to the second component
+    const uint32_t bsite = sizeof(TO) == 8 || !a.keep ? 16u : 32u;
+    const uint32_t bsecond = a.keep ? 16u : (uint32_t)(Tx * Ty) * 16u, brow = (uint32_t)(a.keep ? op.nx : Tx) * bsite;
+    uint32_t b0 = a.keep ? (uint32_t)g0 * bsite
+                         : (uint32_t)(y0 * op.nx + x0 * Ty) * (uint32_t)sizeof(Raw<TO>) + (uint32_t)(j0 * Tx + ci) * bsite;
     // (paired: the components of a site side by side, else two planes)
     auto load_border = [&](const double2 *psi, bool paired) {
         const uint32_t stride = paired ? 32u : 16u, off1 = paired ? 16u : plane;
@@ -521,6 +532,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
         opaque(own);
         opaque(r0);
         opaque(g0);
+        opaque(b0);
     };
     // u_p = cw (A - sig) u_{p-1} - ca u_{p-1} - cb u_{p-2} from LDS and R into LDS,
     // u_{p-1} into R; store(k, u_p) per row
@@ -706,8 +718,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                 const __amdgpu_buffer_rsrc_t ub = row_rsrc(basis + (size_t)(p - 2) * a.vstride, vec_bytes);
                 // u_p into LDS and (the tile itself) memory, u_{p-1} into the registers
                 advance(gxh, gyh, sig, inv_g1, ca, cb, R, [&](int k, const Sp &u) {
-                    st_site(ub, own >> k & 1u ? (uint32_t)(g0 + k * op.nx) * (uint32_t)sizeof(Raw<TO>) : kOob,
-                            to_raw<TO>(u));
+                    st_site(ub, own >> k & 1u ? b0 + (uint32_t)k * brow : kOob, bsecond, to_raw<TO>(u));
                 });
                 const bool last = p == a.m;
                 ++epoch;
@@ -801,13 +812,14 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                         constexpr int kPart = K <= 4 ? K : (K + 1) / 2;
 #pragma unroll
             for (int kb = 0; kb < K; kb += kPart) {
-                uint32_t site[kPart];
+                uint32_t site[kPart], boff[kPart];
                 Sp c[kPart];
 #pragma unroll
                 for (int q = 0; q < kPart; ++q) {
                     const int k = kb + q;
                     const bool on = k < K && (own >> k & 1u);
-                    site[q] = on ? (uint32_t)(g0 + k * op.nx) : kOob / 64u;
+                    site[q] = (uint32_t)(g0 + k * op.nx);
+                    boff[q] = on ? b0 + (uint32_t)k * brow : kOob;
                     const uint32_t off = on ? site[q] * 16u : kOob;
                     const double2 p0 = ld16<double2>(i0, off), p1 = ld16<double2>(i1, off);
                     c[q].r0 = c1r * p0.x - c1i * p0.y;
@@ -818,7 +830,8 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                 auto load = [&](int j, auto pol, Raw<TO>(&v)[kPart]) {
                     const __amdgpu_buffer_rsrc_t ub = row_rsrc(basis + (size_t)(j - 2) * a.vstride, vec_bytes);
 #pragma unroll
-                    for (int q = 0; q < kPart; ++q) v[q] = ld_site_at<TO, decltype(pol)::value>(ub, site[q] * (uint32_t)sizeof(Raw<TO>));
+                    for (int q = 0; q < kPart; ++q) 
+                        v[q] = ld_site_at<TO, decltype(pol)::value>(ub, boff[q], bsecond);
                 };
                 auto add = [&](int j, const Raw<TO>(&v)[kPart]) {
                     const double cr = sh.coef[2 * j], cim = sh.coef[2 * j + 1];
