@@ -5,9 +5,8 @@
 // exponentials, the recombination) whatever the number of packets.
 //
 // Launch shape.  The sweeps of all packets use one common number R of rows per
-// chunk: the smallest power of two (>= 16) for which the batch has at most
-// eight block entries per resident workgroup, or one chunk per strip when
-// even that is more.  A packet's tasks (strip, chunk) are padded to a
+// chunk: the one whose entries, spread over the resident workgroups, finish first
+// (default_rows).  A packet's tasks (strip, chunk) are padded to a
 // multiple of four so that a block entry's waves belong to one packet; the
 // entries of a packet form a contiguous segment (partials slots).  The
 // recombination gives every packet a number of workgroups proportional to its
@@ -15,6 +14,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -172,29 +172,70 @@ const char *batch_validate(const dl_params *params, int n)
     return nullptr;
 }
 
-// Task and workgroup tables for rows_per_chunk R (0: the default choice):
-// the smallest power of two >= 16 with at most eight block entries per
-// resident workgroup, or one chunk per strip when even that is more (256
-// packets of 128^2..512^2, 2 resident workgroups per CU, ms per step:
-// R = 32 5.54, 64 5.58, 128 5.75).
+// Rows of the longest list when entries of these costs go to G workgroups, longest
+// first and each to the least loaded.
+long longest_list(std::vector<long> &cost, int G)
+{
+    std::sort(cost.begin(), cost.end(), std::greater<long>());
+    if (cost.size() <= (size_t)G) return cost.empty() ? 0 : cost[0];
+    std::vector<long> heap(cost.begin(), cost.begin() + G);
+    std::make_heap(heap.begin(), heap.end(), std::greater<long>());
+    for (size_t e = G; e < cost.size(); ++e) {
+        std::pop_heap(heap.begin(), heap.end(), std::greater<long>());
+        heap.back() += cost[e];
+        std::push_heap(heap.begin(), heap.end(), std::greater<long>());
+    }
+    return *std::max_element(heap.begin(), heap.end());
+}
+
+// Rows per chunk of the sweeps: from 16 in steps of four or a sixteenth, the one
+// whose longest list of entries is shortest.  Short chunks spend their rows in the
+// march's start, long ones do not spread evenly over the workgroups (more than
+// eight entries each always do, so those sizes are passed over).  Beyond kLongRows
+// rows one round of entries is all there is, and its gain on paper is not there:
+// 128 packets of 128^2..512^2, 144 rows against 68, complex64 12.80 and 12.73 ms,
+// complex128 21.81 and 21.44.  Below 16 rows the start of the march weighs more than
+// entries on idle workgroups give (8 packets of 150^2..400^2, 8 rows against 16: 1.37
+// and 1.29 ms).  This choice against the smallest power of two with at most eight
+// entries a workgroup, per call of four steps: 128 packets complex64 12.75 against
+// 13.58 ms, 100 of 90^2..250^2 complex64 4.76 and 5.15, 40 of 150^2..400^2 3.53 and 3.96
+// (complex128 5.08 and 5.23).
+int default_rows(const std::vector<dl_params> &params, int G)
+{
+    int max_ny = 0;
+    for (const dl_params &p : params) max_ny = std::max(max_ny, p.ny);
+    int best = 0;
+    long best_len = 0;
+    std::vector<long> cost;
+    constexpr int kLongRows = 96;
+    for (int R = 16; best == 0 || R <= kLongRows; R += std::max(4, R / 64 * 4)) {
+        size_t entries = 0;
+        for (const dl_params &p : params) entries += ceil_div((size_t)strips(p.nx, 2) * ceil_div(p.ny, R), dl::kWaves);
+        if (entries > (size_t)8 * G && R < max_ny) continue;  // (when even whole strips are more, those)
+        cost.clear();
+        for (const dl_params &p : params) {
+            const int ns = strips(p.nx, 2), nch = (int)ceil_div(p.ny, R), tail = p.ny - (nch - 1) * R;
+            // ns (nch - 1) full chunks come first, four tasks to an entry
+            const int full = (int)ceil_div((size_t)ns * (nch - 1), dl::kWaves);
+            const int all = (int)ceil_div((size_t)ns * nch, dl::kWaves);
+            for (int e = 0; e < all; ++e) cost.push_back((e < full ? R : tail) + DL_BATCH_ENTRY_ROWS);
+        }
+        const long len = longest_list(cost, G);
+        if (best == 0 || len <= best_len) {
+            best = R;
+            best_len = len;
+        }
+        if (R >= max_ny) break;
+    }
+    return best;
+}
+
+// Task and workgroup tables for rows_per_chunk R (0: default_rows).
 dl_status build_tables(dl_batch *b, int rows_per_chunk)
 {
     const int n = b->n;
     const std::vector<dl_params> &params = b->p;
-    int R = rows_per_chunk;
-    if (R <= 0) {
-        const size_t target = (size_t)8 * dl::kBatchWgsPerCu * b->cus;
-        int max_ny = 0;
-        for (int i = 0; i < n; ++i) max_ny = std::max(max_ny, params[i].ny);
-        R = 16;
-        for (;;) {
-            size_t e = 0;
-            for (int i = 0; i < n; ++i)
-                e += ceil_div((size_t)strips(params[i].nx, 2) * ceil_div(params[i].ny, R), dl::kWaves);
-            if (e <= target || R >= max_ny) break;
-            R *= 2;
-        }
-    }
+    const int R = rows_per_chunk > 0 ? rows_per_chunk : default_rows(params, dl::kBatchWgsPerCu * b->cus);
     if (R < 4) return b->fail(DL_ERR_INVALID, "rows per chunk must be >= 4");
     b->rows = R;
     std::vector<dl::BatchBlock> blk[dl::kGridKinds];
