@@ -155,7 +155,11 @@ constexpr int kChainLen = 1 + 2 * kMaxM;  // k_eff, alpha_1.., gamma_1.. of a st
 // exchange buffers: two epochs of the partial sums (ten words per workgroup
 // and per copy of a group's sums) and of the published sites (eight words each)
 constexpr size_t kCommRed = sizeof(unsigned long long) * 2 * 10 * (kResidentWgs + 128);
-constexpr size_t kCommBytes = kCommRed + sizeof(unsigned long long) * 2 * 8 * (size_t)kResidentSlots * kResidentWgs;
+constexpr size_t comm_bytes(int slots, int wgs)
+{
+    return kCommRed + sizeof(unsigned long long) * 2 * 8 * (size_t)slots * (size_t)wgs;
+}
+constexpr size_t kCommBytes = comm_bytes(kResidentSlots, kResidentWgs);  // the most any grid takes
 // Whether a run of `rows` rows per thread goes with two tile buffers in LDS.
 constexpr bool resident_two_buffers(int rows) { return rows <= 4; }
 struct ResidentTiles {
@@ -163,6 +167,7 @@ struct ResidentTiles {
     __host__ __device__ int x0(int i, int nx) const { return (int)((long long)i * nx / ntx); }
     __host__ __device__ int y0(int j, int ny) const { return (int)((long long)j * ny / nty); }
     __host__ __device__ int slots() const { return 2 * tx + 2 * ty + 4; }
+    size_t comm() const { return comm_bytes(slots(), ntx * nty); }
     // the tile with a two-site rim (a spare site per plane, two planes per
     // buffer), at least the scratch of the small exponential
     size_t lds_bytes() const
@@ -218,7 +223,7 @@ hipError_t launch_resident_eigen(const ResidentArgs &a, hipStream_t st);
 void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *stats, int first, int n, double reps,
                             double rabs, hipStream_t st);
 // Exchange buffers, epoch and ticks to zero (a new workspace, or after a timeout).
-void launch_zero_comm(void *comm, Scalars *sc, unsigned long long *ticks, hipStream_t st);
+void launch_zero_comm(void *comm, size_t bytes, Scalars *sc, unsigned long long *ticks, hipStream_t st);
 
 // One term of the recombination during a second Lanczos run (the basis is not
 // stored): out = c_1 psi for p = 1, out += c_p u_p for p = 2..k_eff; the

@@ -30,9 +30,10 @@ Layout plan(const dl_params &p, int mode, int k_eigen)
     const bool eig = mode == DL_MODE_EIGEN || mode == DL_MODE_EIGEN_REORTH;
     L.ab_len = std::max(m, eig ? k_eigen + 1 : 0) + 3;
     size_t off = 0;
-    if (dl::resident_tiles(p.nx, p.ny, dl::kResidentWgs).rows > 0) {
+    const dl::ResidentTiles rt = dl::resident_tiles(p.nx, p.ny, dl::kResidentWgs);
+    if (rt.rows > 0) {
         L.comm = off;
-        off = align256(off + dl::kCommBytes);
+        off = align256(off + rt.comm());
     }
     L.sc = off;
     off = align256(off + sizeof(dl::Scalars));
@@ -410,7 +411,7 @@ unsigned long long *ticks_of(const dl_context *ctx)
 void clear_failure(dl_context *ctx, int status)
 {
     // after a timeout the workgroups may have left at different epochs
-    if (status == dl::kStatusTimeout) dl::launch_zero_comm(ctx->ws + ctx->L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
+    if (status == dl::kStatusTimeout) dl::launch_zero_comm(ctx->ws + ctx->L.comm, ctx->L.sc - ctx->L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
     dl::launch_reset(ctx->sc(), ctx->stream);
 }
 
@@ -561,7 +562,7 @@ dl_status dirac_lanczos_init(const dl_params *params, void *workspace, size_t ws
     ctx->L = L;
     ctx->cus = prop.multiProcessorCount;
     set_tiles(ctx, 0);
-    if (ctx->resident.rows > 0) dl::launch_zero_comm(ctx->ws + L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
+    if (ctx->resident.rows > 0) dl::launch_zero_comm(ctx->ws + L.comm, L.sc - L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
     dl::launch_reset(ctx->sc(), ctx->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {

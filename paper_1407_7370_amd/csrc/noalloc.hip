@@ -20,10 +20,10 @@ using namespace dlh;
 
 namespace {
 
-// The scratch starts with the exchange buffers of the resident steps (zero when
-// the program starts; a grid that does not take that path begins behind them,
-// where the scalars with the epoch are in every layout), then 64 MiB for the
-// rest of the workspace and the resident steps' small arrays.
+// The scratch starts with room for the largest exchange buffers of the resident
+// steps (zero when the program starts), so that the scalars with the buffers' epoch
+// are in one place for every grid; then 64 MiB for the rest of the workspace and
+// the resident steps' small arrays.
 constexpr size_t kProblemBytes = size_t(64) << 20;
 constexpr size_t kExchange = align256(dl::kCommBytes);
 constexpr size_t kScratchBytes = kExchange + kProblemBytes + (size_t(128) << 10);
@@ -59,8 +59,14 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     if (validate(params)) return DL_ERR_INVALID;
     if (!psi_v || n_steps < 0 || !(dt != 0.0) || !std::isfinite(dt) || !std::isfinite(t0)) return DL_ERR_INVALID;
     if (params->pulse_kind == DL_PULSE_FOURIER_SIN2 && !params->coef) return DL_ERR_INVALID;
-    const Layout L = plan(*params, DL_MODE_STEP, 0);
+    Layout L = plan(*params, DL_MODE_STEP, 0);
     if (L.total - L.resident > kProblemBytes) return DL_ERR_WORKSPACE;  // beyond the static scratch
+    // the exchange buffers of a layout at the scratch's start, the rest behind
+    // the largest
+    const size_t shift = kExchange - L.sc;
+    for (size_t Layout::*at : {&Layout::sc, &Layout::chain, &Layout::ticks, &Layout::alpha, &Layout::gamma,
+                               &Layout::partials, &Layout::fields, &Layout::stats, &Layout::vecs, &Layout::total})
+        L.*at += shift;
     if (n_steps == 0) return DL_OK;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return DL_ERR_DEVICE;
@@ -89,9 +95,8 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     dl_context ctx;
     ctx.p = p;
     ctx.stream = st;
-    const size_t skip = L.sc == 0 ? kExchange : 0;  // no exchange buffers in this layout
-    ctx.ws = static_cast<char *>(ws) + skip;
-    ctx.ws_bytes = kScratchBytes - skip;
+    ctx.ws = static_cast<char *>(ws);
+    ctx.ws_bytes = kScratchBytes;
     ctx.L = L;
     ctx.cus = cus;
     configure_launch(&ctx);

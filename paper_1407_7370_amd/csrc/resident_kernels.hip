@@ -1020,10 +1020,10 @@ void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *st
     hipLaunchKernelGGL(k_resident_bounds, dim3(n), dim3(64), 0, st, chain, sc, stats, first, reps, rabs);
 }
 
-void launch_zero_comm(void *comm, Scalars *sc, unsigned long long *ticks, hipStream_t st)
+void launch_zero_comm(void *comm, size_t bytes, Scalars *sc, unsigned long long *ticks, hipStream_t st)
 {
     hipLaunchKernelGGL(k_zero_words, dim3(1024), dim3(kBlock), 0, st, static_cast<unsigned long long *>(comm),
-                       kCommBytes / 8, sc, ticks);
+                       bytes / 8, sc, ticks);
 }
 
 }  // namespace dl
