@@ -282,10 +282,11 @@ dl_status dirac_lanczos_step_adaptive(dl_context *ctx, void *psi, double t0, dou
  * tol are one eigenvalue and keep their smallest bound; the call stops at
  * the first checkpoint with n_wanted values and reports the lowest n_wanted.
  * reorth != 0: full
- * reorthogonalisation applied twice (Sec. 2), as classical Gram-Schmidt
- * against all stored vectors (h = Q^H z, z -= Q h, two passes; the first
- * pass also removes the alpha_i q_i and beta_{i-1} q_{i-1} terms of the
- * recurrence, alpha_i = Re h_i of that pass), a workspace sized for
+ * reorthogonalisation (Sec. 2): the recurrence's terms alpha_i q_i and
+ * beta_{i-1} q_{i-1} are subtracted, then classical Gram-Schmidt runs against all
+ * stored vectors (h = Q^H z, z -= Q h), a second time where the first pass
+ * removed more than 1/128 of the vector (what is left is rounding either
+ * way); a workspace sized for
  * DL_MODE_EIGEN_REORTH with k_eigen >= k_max; every 64 iterations the
  * Ritz values of the current T are computed on the host, and the recurrence
  * stops early once n_wanted clusters have converged (the values are then
