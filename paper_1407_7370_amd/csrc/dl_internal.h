@@ -37,7 +37,6 @@ struct Scalars {
     // (0: m), and the small exponential predicts knext for the next step
     int kmin, kmax, knext;
     double ktol;                   // per-step bound on the error estimate (0: off)
-    unsigned int epoch;            // last epoch of the workspace's exchange buffers (resident steps; never reset)
     int again;                     // full reorthogonalisation: a second pass follows
 };
 // Scalars::status of a call whose resident step waited too long (0 ok, 3 a
@@ -205,7 +204,7 @@ struct ResidentArgs {
     char *keep;                // per step (keep_step apart): Scalars, alpha and gamma for the adjoint, or NULL
     size_t keep_step, keep_alpha, keep_gamma;
     unsigned long long *red, *halo;  // exchange buffers
-    unsigned int *epoch;             // their last epoch
+    uint32_t epoch;                  // the epoch before the launch's first (set by the launch functions)
     unsigned long long *ticks;       // per kernel class, the launch's 100 MHz ticks are added (timing), or NULL
     __host__ __device__ double2 *state_in(int s) const
     {
@@ -218,12 +217,12 @@ struct ResidentArgs {
 ResidentTiles resident_tiles(int nx, int ny, int wgs);
 // Cooperative launch of n_steps <= kResidentSteps steps (any error: nothing ran).
 hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st);
-// Cooperative launch of a.eig's iterations (op, t, sc, red, halo, epoch and eig of a).
+// Cooperative launch of a.eig's iterations (op, t, sc, red, halo and eig of a).
 hipError_t launch_resident_eigen(const ResidentArgs &a, hipStream_t st);
 void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *stats, int first, int n, double reps,
                             double rabs, hipStream_t st);
-// Exchange buffers, epoch and ticks to zero (a new workspace, or after a timeout).
-void launch_zero_comm(void *comm, size_t bytes, Scalars *sc, unsigned long long *ticks, hipStream_t st);
+// Exchange buffers and ticks to zero (a new workspace, or after a timeout).
+void launch_zero_comm(void *comm, size_t bytes, unsigned long long *ticks, hipStream_t st);
 
 // One term of the recombination during a second Lanczos run (the basis is not
 // stored): out = c_1 psi for p = 1, out += c_p u_p for p = 2..k_eff; the

@@ -372,7 +372,6 @@ dl_status run_resident(dl_context *ctx, const Engine &e, const dl::Op &op, const
     a.keep_gamma = r.keep_gamma;
     a.red = reinterpret_cast<unsigned long long *>(ws + L.comm);
     a.halo = reinterpret_cast<unsigned long long *>(ws + L.comm + dl::kCommRed);
-    a.epoch = &ctx->sc()->epoch;
     a.ticks = ctx->timing ? ticks_of(ctx) : nullptr;
     for (int i = 0; i < n; i += dl::kResidentSteps) {
         a.n_steps = std::min(dl::kResidentSteps, n - i);
@@ -410,8 +409,7 @@ unsigned long long *ticks_of(const dl_context *ctx)
 
 void clear_failure(dl_context *ctx, int status)
 {
-    // after a timeout the workgroups may have left at different epochs
-    if (status == dl::kStatusTimeout) dl::launch_zero_comm(ctx->ws + ctx->L.comm, ctx->L.sc - ctx->L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
+    if (status == dl::kStatusTimeout) dl::launch_zero_comm(ctx->ws + ctx->L.comm, ctx->L.sc - ctx->L.comm, ticks_of(ctx), ctx->stream);
     dl::launch_reset(ctx->sc(), ctx->stream);
 }
 
@@ -562,7 +560,7 @@ dl_status dirac_lanczos_init(const dl_params *params, void *workspace, size_t ws
     ctx->L = L;
     ctx->cus = prop.multiProcessorCount;
     set_tiles(ctx, 0);
-    if (ctx->resident.rows > 0) dl::launch_zero_comm(ctx->ws + L.comm, L.sc - L.comm, ctx->sc(), ticks_of(ctx), ctx->stream);
+    if (ctx->resident.rows > 0) dl::launch_zero_comm(ctx->ws + L.comm, L.sc - L.comm, ticks_of(ctx), ctx->stream);
     dl::launch_reset(ctx->sc(), ctx->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -855,7 +853,6 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
     ra.sc = sc;
     ra.red = reinterpret_cast<unsigned long long *>(ws + E.comm);
     ra.halo = reinterpret_cast<unsigned long long *>(ws + E.comm + dl::kCommRed);
-    ra.epoch = &sc->epoch;
     ra.eig.alpha = alpha;
     ra.eig.gamma = gamma;
     auto resident = [&](int p0, int p1) {

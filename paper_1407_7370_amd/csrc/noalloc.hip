@@ -21,8 +21,7 @@ using namespace dlh;
 namespace {
 
 // The scratch starts with room for the largest exchange buffers of the resident
-// steps (zero when the program starts), so that the scalars with the buffers' epoch
-// are in one place for every grid; then 64 MiB for the rest of the workspace and
+// steps (zero when the program starts), which nothing else overwrites; then 64 MiB for the rest of the workspace and
 // the resident steps' small arrays.
 constexpr size_t kProblemBytes = size_t(64) << 20;
 constexpr size_t kExchange = align256(dl::kCommBytes);

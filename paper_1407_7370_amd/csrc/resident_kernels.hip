@@ -22,8 +22,9 @@
 // epoch matches, so data and validity arrive together (one store-to-load
 // latency per iteration).  Words alternate between two buffers; a workgroup
 // writes epoch e + 2 only after it has seen every partial of e + 1, which each
-// workgroup sends after it has consumed epoch e.  Epoch numbers grow over the
-// life of a workspace (Scalars::epoch), so words of earlier calls never match.
+// workgroup sends after it has consumed epoch e.  Every launch of the process
+// has epoch numbers of its own (reserve_epochs), so words left by earlier launches,
+// of this or another context on the same memory, never match.
 //
 // The partial sums of more than kDirect workgroups go through kLeaders of them
 // (each adds its group's and posts the group's sum), because every workgroup
@@ -43,6 +44,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "sweeps.h"
 
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
     }
     unsigned long long *const red = a.red, *const halo = a.halo;
     const size_t halo_buf = (size_t)NW * NS * nwg;
-    uint32_t epoch = *a.epoch;
+    uint32_t epoch = a.epoch;
     const unsigned long long started = wall_clock64();
 
     const bool direct = nwg <= kDirect;
@@ -658,12 +660,9 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                     a.eig.o2[g + 1] = make_double2(R[k].r1, R[k].i1);
                 }
         }
-        if (wg == 0 && t == 0) {
-            if (timeout) {
-                sc->status = kStatusTimeout;
-                sc->kstop = -1;
-            }
-            *a.epoch = epoch;
+        if (timeout && wg == 0 && t == 0) {
+            sc->status = kStatusTimeout;
+            sc->kstop = -1;
         }
         return;
     }
@@ -935,7 +934,6 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
             sc->status = timeout ? kStatusTimeout : 3;
             sc->kstop = -1;
         }
-        *a.epoch = epoch;
         if (a.ticks)
             for (int q = 0; q < 5; ++q) a.ticks[q] += clk[q];
     }
@@ -960,11 +958,9 @@ __global__ __launch_bounds__(64) void k_resident_bounds(const double *chain, con
     if (lane == 0) stats[step].round_bound = rb;
 }
 
-__global__ __launch_bounds__(kBlock) void k_zero_words(unsigned long long *p, size_t n, Scalars *sc,
-                                                       unsigned long long *ticks)
+__global__ __launch_bounds__(kBlock) void k_zero_words(unsigned long long *p, size_t n, unsigned long long *ticks)
 {
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) p[i] = 0ull;
-    if (blockIdx.x == 0 && threadIdx.x == 0) sc->epoch = 0u;
     if (blockIdx.x == 0 && threadIdx.x < 5) ticks[threadIdx.x] = 0ull;
 }
 
@@ -986,13 +982,26 @@ ResidentKernel pick_rows(int k)
 
 }  // namespace
 
-static hipError_t launch_tiles(const ResidentArgs &a, ResidentKernel kernel, hipStream_t st)
+// Epochs base + 1 .. base + n for one launch: never 0 (cleared buffers), and used
+// again only after the 32-bit count has gone round (over three hours of launches).
+static uint32_t reserve_epochs(uint32_t n)
+{
+    static std::atomic<uint32_t> last{0};
+    uint32_t base;
+    do
+        base = last.fetch_add(n, std::memory_order_relaxed);
+    while (base + n < base);
+    return base;
+}
+
+static hipError_t launch_tiles(const ResidentArgs &a, int epochs, ResidentKernel kernel, hipStream_t st)
 {
     const size_t lds = a.t.lds_bytes();
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
     ResidentArgs args = a;
+    args.epoch = reserve_epochs((uint32_t)epochs);
     void *params[] = {&args};
     return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(kernel), dim3(a.t.ntx * a.t.nty), dim3(kRBlock),
                                       params, (unsigned)lds, st);
@@ -1003,14 +1012,18 @@ hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st)
     constexpr int kAll = kTermPot | kTermB;
     const bool terms = op_terms(a.op) != 0;
     const int k = a.t.rows;
-    return launch_tiles(a, mixed ? (terms ? pick_rows<float2, kAll, false>(k) : pick_rows<float2, 0, false>(k))
-                                 : (terms ? pick_rows<double2, kAll, false>(k) : pick_rows<double2, 0, false>(k)), st);
+    // an epoch per iteration and one for the norm of the new state
+    return launch_tiles(a, a.n_steps * (a.m + 1),
+                        mixed ? (terms ? pick_rows<float2, kAll, false>(k) : pick_rows<float2, 0, false>(k))
+                              : (terms ? pick_rows<double2, kAll, false>(k) : pick_rows<double2, 0, false>(k)),
+                        st);
 }
 
 hipError_t launch_resident_eigen(const ResidentArgs &a, hipStream_t st)
 {
     const int k = a.t.rows;
-    return launch_tiles(a, op_terms(a.op) != 0 ? pick_rows<double2, kTermPot | kTermB, true>(k) : pick_rows<double2, 0, true>(k),
+    return launch_tiles(a, a.eig.p1 - a.eig.p0 + 1,
+                        op_terms(a.op) != 0 ? pick_rows<double2, kTermPot | kTermB, true>(k) : pick_rows<double2, 0, true>(k),
                         st);
 }
 
@@ -1020,10 +1033,10 @@ void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *st
     hipLaunchKernelGGL(k_resident_bounds, dim3(n), dim3(64), 0, st, chain, sc, stats, first, reps, rabs);
 }
 
-void launch_zero_comm(void *comm, size_t bytes, Scalars *sc, unsigned long long *ticks, hipStream_t st)
+void launch_zero_comm(void *comm, size_t bytes, unsigned long long *ticks, hipStream_t st)
 {
     hipLaunchKernelGGL(k_zero_words, dim3(1024), dim3(kBlock), 0, st, static_cast<unsigned long long *>(comm),
-                       bytes / 8, sc, ticks);
+                       bytes / 8, ticks);
 }
 
 }  // namespace dl

@@ -158,3 +158,29 @@ def test_adjoint_without_kept_bases(torch_cuda):
     prop.close()
     assert res[0][0] == res[1][0]
     assert np.array_equal(res[0][1], res[1][1])
+
+
+def test_contexts_on_one_workspace(torch_cuda, orc):
+    """Two grids' contexts on the same workspace memory, used in turn: words that
+    one leaves in the other's exchange buffers are never taken for its own."""
+    from paper_1407_7370_amd import binding
+    torch = torch_cuda
+    dt, m, n = 1e-4, 6, 3
+    probs = [box(64, 60, 1, 1), box(200, 170, 0, 0, **FIELDS)]
+    params = [binding.make_params(p, m, binding.DL_PREC_FP64) for p in probs]
+    size = max(binding.dirac_lanczos_workspace_bytes(p[0]) for p in params)
+    ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+    ctxs = [binding.dirac_lanczos_init(p[0], ws.data_ptr(), size, torch.cuda.current_stream().cuda_stream) for p in params]
+    psi0 = [packets.random_spinor(p, 3) * 1e-2 + packets.gaussian_packet(p, 1.0, (1.0, -2.0)) for p in probs]
+    psi = [torch.from_numpy(p).cuda() for p in psi0]
+    for turn in range(4):
+        for c, p in zip(ctxs, psi):
+            say(f"one workspace, turn {turn}, {tuple(p.shape)}")
+            # (synchronous calls: asynchronous ones keep their status in the workspace)
+            assert binding.dirac_lanczos_step(c, p.data_ptr(), turn * n * dt, dt, n, (binding.DlStepStat * n)()) == 0
+    for c in ctxs:
+        binding.dirac_lanczos_destroy(c)
+    phase = dt * (C * C + 2 * C / 0.1 + 10 * C)
+    for prob, p, p0 in zip(probs, psi, psi0):
+        ref, _ = orc.propagate(prob, p0, 0.0, dt, 4 * n, m)
+        assert hz.rel_l2(p.cpu().numpy(), ref) <= 64 * 4 * n * phase * EPS
