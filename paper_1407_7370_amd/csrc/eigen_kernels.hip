@@ -407,7 +407,9 @@ __global__ __launch_bounds__(kBlock) void k_ritz_window(const double *__restrict
         for (int i = 0; i < kWaves; ++i) s += cnt[i];
         return s;
     };
-    const double slo = ldexp(lo, -ex), shi = ldexp(hi, -ex);
+    // every value lies in [-1, 1]; bounds far outside would overflow the minors
+    // between two rescalings
+    const double slo = fmin(fmax(ldexp(lo, -ex), -2.0), 2.0), shi = fmin(fmax(ldexp(hi, -ex), -2.0), 2.0);
     if (w == 0) {
         const int c = count(lane == 0 ? slo : shi);
         if (lane < 2) cnt[lane] = c;

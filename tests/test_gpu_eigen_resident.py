@@ -107,3 +107,32 @@ def test_breakdown(torch_cuda, orc, k):
     again, _ = prop.eigen(torch.from_numpy(psi0).cuda(), k, -WIDE, WIDE, 1e-6, n_wanted=8)
     prop.close()
     assert np.array_equal(again, ev)
+
+
+@pytest.mark.parametrize("e_lo,e_hi", [(-1e300, 1e300), (-1e30, 1e30), (0.0, 1e30), (0.0, 1e300), (-1e25, 0.0)])
+def test_windows_far_beyond_the_spectrum(torch_cuda, orc, e_lo, e_hi):
+    """Finite bounds far outside the spectrum stand for open ends: the values of
+    the first checkpoint's T_64 in the window (one cluster each with tol above the
+    spectrum's width), as numpy has them for the oracle's T_64, and bit for bit
+    those of a window that ends just outside the spectrum."""
+    from paper_1407_7370_amd.binding import Propagator
+    say(f"eigen window ({e_lo}, {e_hi}]")
+    prob = box(96, 90, 1, 0, True)
+    psi0 = packets.random_spinor(prob, 11)
+    k = 130
+    prop = Propagator(prob, 1, "fp64", k_eigen=k)
+    psi = torch_cuda.from_numpy(psi0).cuda()
+    ev, bd = prop.eigen(psi, k, e_lo, e_hi, 4 * WIDE, n_wanted=1)
+    ev2, bd2 = prop.eigen(psi, k, max(e_lo, -WIDE), min(e_hi, WIDE), 4 * WIDE, n_wanted=1)
+    prop.close()
+    _, al, be = orc.lanczos_plain(prob, psi0, 64)
+    w, z = np.linalg.eigh(np.diag(al[:64]) + np.diag(be[:63], 1) + np.diag(be[:63], -1))
+    inside = (w > e_lo) & (w <= e_hi)
+    # no value of a random start's T_64 has converged: alpha and beta agree to the
+    # rounding of H's norm times a modest growth, its eigenvectors to that over the
+    # distance of neighbouring values
+    err = 1e4 * EPS * (C * C + 2 * C / 0.1 + 20 * C)
+    assert len(ev) == 1 and np.abs(w).min() > 1.0
+    assert abs(ev[0] - w[inside].mean()) <= err
+    assert abs(bd[0] - be[63] * np.linalg.norm(z[-1, inside])) <= err * (1.0 + be[63] / np.diff(w).min())
+    assert np.array_equal(ev, ev2) and np.array_equal(bd, bd2)
