@@ -316,7 +316,7 @@ dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, 
     const dl::Op opf = ctx->op(dt), opb = ctx->op(-dt), op1 = ctx->op(1.0);
     const dl_status pend = take_async_failure(ctx);
     if (pend != DL_OK) return pend;
-    dl::launch_reset(ep.sc, st);
+    reset_call(ctx);
     dl::launch_reset(el.sc, st);
     DL_HIP(ctx, hipGetLastError());
 
@@ -379,7 +379,6 @@ dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, 
         DL_HIP(ctx, hipMemcpyAsync(&status, &sc->status, sizeof(int), hipMemcpyDeviceToHost, st));
         DL_HIP(ctx, hipStreamSynchronize(st));
         if (status == 0) return DL_OK;
-        if (status == dl::kStatusTimeout) clear_failure(ctx, status);
         return ctx->status_fail(status, std::string("in the ") + what);
     };
 

@@ -17,9 +17,8 @@
 namespace dlh {
 
 struct Layout {
-    // comm: exchange buffers of the resident steps, at the start of every
-    // workspace of a grid that takes them (their words must never be
-    // overwritten by anything else); chain, ticks: see dl::ResidentArgs
+    // comm: exchange buffers of the resident steps (grids that take them),
+    // cleared by every call that uses them; chain, ticks: see dl::ResidentArgs
     size_t comm = 0, chain = 0, ticks = 0;
     size_t resident = 0;  // bytes of the three regions
     size_t sc = 0, alpha = 0, gamma = 0, partials = 0, fields = 0, stats = 0, vecs = 0, total = 0;
@@ -306,8 +305,8 @@ void configure_launch(dl_context *ctx);
 // synchronous entry point that resets the scalars calls it first.
 dl_status take_async_failure(dl_context *ctx);
 unsigned long long *ticks_of(const dl_context *ctx);
-// Scalars (and after a timeout the exchange buffers) back to a usable state.
-void clear_failure(dl_context *ctx, int status);
+// Scalars and exchange buffers as a call's first launch needs them (see k_reset).
+void reset_call(dl_context *ctx, int keep_status = 0, int kmin = 0, int kmax = 0, double ktol = 0.0);
 
 // Eigen mode with full reorthogonalisation (eigen.cpp); vecs (device, may be
 // NULL) receives the Ritz vectors of the reported values.

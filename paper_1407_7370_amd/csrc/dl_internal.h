@@ -158,6 +158,7 @@ constexpr size_t comm_bytes(int slots, int wgs)
 {
     return kCommRed + sizeof(unsigned long long) * 2 * 8 * (size_t)slots * (size_t)wgs;
 }
+static_assert(kCommRed % 16 == 0, "the exchange buffers are cleared in 16-byte words");
 constexpr size_t kCommBytes = comm_bytes(kResidentSlots, kResidentWgs);  // the most any grid takes
 // Whether a run of `rows` rows per thread goes with two tile buffers in LDS.
 constexpr bool resident_two_buffers(int rows) { return rows <= 4; }
@@ -166,7 +167,7 @@ struct ResidentTiles {
     __host__ __device__ int x0(int i, int nx) const { return (int)((long long)i * nx / ntx); }
     __host__ __device__ int y0(int j, int ny) const { return (int)((long long)j * ny / nty); }
     __host__ __device__ int slots() const { return 2 * tx + 2 * ty + 4; }
-    size_t comm() const { return comm_bytes(slots(), ntx * nty); }
+    size_t comm() const { return rows > 0 ? comm_bytes(slots(), ntx * nty) : 0; }
     // the tile with a two-site rim (a spare site per plane, two planes per
     // buffer), at least the scratch of the small exponential
     size_t lds_bytes() const
@@ -221,8 +222,6 @@ hipError_t launch_resident(const ResidentArgs &a, bool mixed, hipStream_t st);
 hipError_t launch_resident_eigen(const ResidentArgs &a, hipStream_t st);
 void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *stats, int first, int n, double reps,
                             double rabs, hipStream_t st);
-// Exchange buffers and ticks to zero (a new workspace, or after a timeout).
-void launch_zero_comm(void *comm, size_t bytes, unsigned long long *ticks, hipStream_t st);
 
 // One term of the recombination during a second Lanczos run (the basis is not
 // stored): out = c_1 psi for p = 1, out += c_p u_p for p = 2..k_eff; the
@@ -301,8 +300,10 @@ void launch_apply(const Op &op, const Tiles &t, const double2 *x, double2 *y, do
                   double gyh, hipStream_t st);
 void launch_reset(Scalars *sc, hipStream_t st);
 // Reset at the start of a step call (see k_reset): keep_status for
-// asynchronous calls, the adaptive-dimension parameters (ktol = 0: off).
-void launch_reset_call(Scalars *sc, int keep_status, int kmin, int kmax, double ktol, hipStream_t st);
+// asynchronous calls, the adaptive-dimension parameters (ktol = 0: off), the
+// exchange buffers to clear (16-byte multiples, or none).
+void launch_reset_call(Scalars *sc, int keep_status, int kmin, int kmax, double ktol, void *comm, size_t comm_bytes,
+                       hipStream_t st);
 // psi <- state (n complex128 values) when sc->steps_done is odd.
 void launch_finish_copy(const Scalars *sc, const double2 *state, double2 *psi, size_t n, int cus, hipStream_t st);
 

@@ -407,10 +407,10 @@ unsigned long long *ticks_of(const dl_context *ctx)
     return reinterpret_cast<unsigned long long *>(ctx->ws + ctx->L.ticks);
 }
 
-void clear_failure(dl_context *ctx, int status)
+void reset_call(dl_context *ctx, int keep_status, int kmin, int kmax, double ktol)
 {
-    if (status == dl::kStatusTimeout) dl::launch_zero_comm(ctx->ws + ctx->L.comm, ctx->L.sc - ctx->L.comm, ticks_of(ctx), ctx->stream);
-    dl::launch_reset(ctx->sc(), ctx->stream);
+    dl::launch_reset_call(ctx->sc(), keep_status, kmin, kmax, ktol, ctx->ws + ctx->L.comm, ctx->resident.comm(),
+                          ctx->stream);
 }
 
 dl_status take_async_failure(dl_context *ctx)
@@ -421,7 +421,7 @@ dl_status take_async_failure(dl_context *ctx)
     dl::Scalars hs;
     DL_HIP(ctx, hipMemcpy(&hs, ctx->sc(), sizeof(hs), hipMemcpyDeviceToHost));
     if (hs.status == 0) return DL_OK;
-    clear_failure(ctx, hs.status);
+    dl::launch_reset(ctx->sc(), ctx->stream);
     DL_HIP(ctx, hipStreamSynchronize(ctx->stream));
     return ctx->status_fail(hs.status, "in an asynchronous call after " + std::to_string(hs.steps_done) + " of its steps");
 }
@@ -560,7 +560,6 @@ dl_status dirac_lanczos_init(const dl_params *params, void *workspace, size_t ws
     ctx->L = L;
     ctx->cus = prop.multiProcessorCount;
     set_tiles(ctx, 0);
-    if (ctx->resident.rows > 0) dl::launch_zero_comm(ctx->ws + L.comm, L.sc - L.comm, ticks_of(ctx), ctx->stream);
     dl::launch_reset(ctx->sc(), ctx->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
@@ -670,8 +669,7 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
 
     // adaptive dimension (ktol > 0): the first step runs m iterations, later
     // ones the dimension the previous step predicted
-    dl::launch_reset_call(sc, async ? 1 : 0, ktol > 0.0 ? kmin : 0, ktol > 0.0 ? m : 0, ktol > 0.0 ? ktol : 0.0,
-                          st);
+    reset_call(ctx, async ? 1 : 0, ktol > 0.0 ? kmin : 0, ktol > 0.0 ? m : 0, ktol > 0.0 ? ktol : 0.0);
     DL_HIP(ctx, hipGetLastError());
     double cum = 0.0;
     int completed = 0, status = 0;
@@ -753,10 +751,7 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
         DL_HIP(ctx, hipMemcpyAsync(psi, state, n * 16, hipMemcpyDeviceToDevice, st));
         DL_HIP(ctx, hipStreamSynchronize(st));
     }
-    if (aborted) {
-        if (status == dl::kStatusTimeout) clear_failure(ctx, status);
-        return ctx->status_fail(status, "after " + std::to_string(completed) + " completed steps");
-    }
+    if (aborted) return ctx->status_fail(status, "after " + std::to_string(completed) + " completed steps");
     return DL_OK;
 }
 
@@ -822,7 +817,7 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
     const double zero[2] = {0.0, 0.0};
     DL_HIP(ctx, hipMemcpyAsync(fields, zero, sizeof(zero), hipMemcpyHostToDevice, st));
     DL_HIP(ctx, hipMemcpyAsync(v[1], psi0, n * 16, hipMemcpyDeviceToDevice, st));
-    dl::launch_reset(sc, st);
+    reset_call(ctx);
     const int K1 = k_max + 1;  // the extra iteration yields beta_k for the bounds
     dl::launch_first(op, t1, v[1], fields, alpha, gamma, sc, partials, K1, 0, st);
     std::vector<double> ha(K1 + 1), hg(K1 + 1);
@@ -842,7 +837,6 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
         }
         DL_HIP(ctx, hipMemcpyAsync(&rec, sc, sizeof(rec), hipMemcpyDeviceToHost, st));
         DL_HIP(ctx, hipStreamSynchronize(st));
-        if (hs.status == dl::kStatusTimeout) clear_failure(ctx, hs.status);
         if (hs.status != 0) return ctx->status_fail(hs.status, "in eigen mode");
         return DL_OK;
     };
@@ -991,7 +985,7 @@ dl_status dirac_lanczos_wait(dl_context *ctx, dl_step_stat *stats, int32_t n_sta
     }
     ctx->async_pending = false;
     if (hs.status != 0) {
-        clear_failure(ctx, hs.status);
+        dl::launch_reset(ctx->sc(), ctx->stream);
         DL_HIP(ctx, hipStreamSynchronize(ctx->stream));
         return ctx->status_fail(hs.status, "after " + std::to_string(hs.steps_done) + " completed steps of the last call");
     }

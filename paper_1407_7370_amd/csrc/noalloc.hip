@@ -21,8 +21,8 @@ using namespace dlh;
 namespace {
 
 // The scratch starts with room for the largest exchange buffers of the resident
-// steps (zero when the program starts), which nothing else overwrites; then 64 MiB for the rest of the workspace and
-// the resident steps' small arrays.
+// steps; then 64 MiB for the rest of the workspace and the resident steps' small
+// arrays.
 constexpr size_t kProblemBytes = size_t(64) << 20;
 constexpr size_t kExchange = align256(dl::kCommBytes);
 constexpr size_t kScratchBytes = kExchange + kProblemBytes + (size_t(128) << 10);
@@ -114,7 +114,7 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     const double kf = -dt * p.c * p.charge;
 
     // every call starts from zeroed scalars and reduction ticket
-    dl::launch_reset(sc, st);
+    reset_call(&ctx);
     if (hipGetLastError() != hipSuccess) return DL_ERR_DEVICE;
     double cum = 0.0;
     int completed = 0, status = 0;
@@ -181,9 +181,6 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     dl::launch_finish_copy(sc, state, psi, n, cus, st);
     if (hipGetLastError() != hipSuccess) return DL_ERR_DEVICE;
     if (stats && hipStreamSynchronize(st) != hipSuccess) return DL_ERR_DEVICE;
-    if (aborted && status == dl::kStatusTimeout) {
-        clear_failure(&ctx, status);
-        return DL_ERR_DEVICE;
-    }
-    return aborted ? DL_ERR_NONFINITE : DL_OK;
+    if (aborted) return status == dl::kStatusTimeout ? DL_ERR_DEVICE : DL_ERR_NONFINITE;
+    return DL_OK;
 }

@@ -22,9 +22,10 @@
 // epoch matches, so data and validity arrive together (one store-to-load
 // latency per iteration).  Words alternate between two buffers; a workgroup
 // writes epoch e + 2 only after it has seen every partial of e + 1, which each
-// workgroup sends after it has consumed epoch e.  Every launch of the process
-// has epoch numbers of its own (reserve_epochs), so words left by earlier launches,
-// of this or another context on the same memory, never match.
+// workgroup sends after it has consumed epoch e.  Every call clears the words
+// first (k_reset), and its launches have epoch numbers of their own
+// (reserve_epochs), so neither what was in the memory before the call nor words
+// of the call's earlier launches match.
 //
 // The partial sums of more than kDirect workgroups go through kLeaders of them
 // (each adds its group's and posts the group's sum), because every workgroup
@@ -958,12 +959,6 @@ __global__ __launch_bounds__(64) void k_resident_bounds(const double *chain, con
     if (lane == 0) stats[step].round_bound = rb;
 }
 
-__global__ __launch_bounds__(kBlock) void k_zero_words(unsigned long long *p, size_t n, unsigned long long *ticks)
-{
-    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) p[i] = 0ull;
-    if (blockIdx.x == 0 && threadIdx.x < 5) ticks[threadIdx.x] = 0ull;
-}
-
 using ResidentKernel = void (*)(ResidentArgs);
 
 template <class TO, int TERMS, bool EIG>
@@ -983,7 +978,8 @@ ResidentKernel pick_rows(int k)
 }  // namespace
 
 // Epochs base + 1 .. base + n for one launch: never 0 (cleared buffers), and used
-// again only after the 32-bit count has gone round (over three hours of launches).
+// again only after the 32-bit count has gone round, which no words outlast: every
+// call clears them, and a launch writes each of them every few epochs.
 static uint32_t reserve_epochs(uint32_t n)
 {
     static std::atomic<uint32_t> last{0};
@@ -1031,12 +1027,6 @@ void launch_resident_bounds(const double *chain, const Scalars *sc, StepStat *st
                             double rabs, hipStream_t st)
 {
     hipLaunchKernelGGL(k_resident_bounds, dim3(n), dim3(64), 0, st, chain, sc, stats, first, reps, rabs);
-}
-
-void launch_zero_comm(void *comm, size_t bytes, unsigned long long *ticks, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_zero_words, dim3(1024), dim3(kBlock), 0, st, static_cast<unsigned long long *>(comm),
-                       bytes / 8, ticks);
 }
 
 }  // namespace dl

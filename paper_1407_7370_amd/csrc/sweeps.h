@@ -1830,10 +1830,15 @@ __global__ __launch_bounds__(kBlock) void k_apply(Op op, Tiles t, const double2 
 // Scalars to the start-of-call state.  keep_status: an asynchronous call
 // leaves a failure of an earlier call in place (its kernels then do nothing)
 // until the host has read it.  kmin, kmax, ktol: adaptive Krylov dimension
-// (ktol = 0: off).
-__global__ void k_reset(Scalars *sc, int keep_status, int kmin, int kmax, double ktol)
+// (ktol = 0: off).  comm: the exchange buffers of resident launches (n 16-byte
+// words), cleared so that nothing else that was in the memory (another context's
+// vectors, epochs of long ago) can pass for a word of the call's launches.
+__global__ __launch_bounds__(kBlock) void k_reset(Scalars *sc, int keep_status, int kmin, int kmax, double ktol,
+                                                  uint4 *comm, size_t n)
 {
-    if (threadIdx.x == 0) {
+    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock)
+        comm[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (!keep_status) sc->status = 0;
         sc->steps_done = 0;
         sc->ticket = 0u;

@@ -184,3 +184,43 @@ def test_contexts_on_one_workspace(torch_cuda, orc):
     for prob, p, p0 in zip(probs, psi, psi0):
         ref, _ = orc.propagate(prob, p0, 0.0, dt, 4 * n, m)
         assert hz.rel_l2(p.cpu().numpy(), ref) <= 64 * 4 * n * phase * EPS
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 60), (300, 280)])  # sums read directly, and through leaders
+@pytest.mark.parametrize("ahead", [1, 2])
+@pytest.mark.parametrize("call", ["step", "async", "eigen"])
+def test_foreign_words_in_the_workspace(torch_cuda, nx, ny, ahead, call):
+    """What another user of the memory left in a workspace between two calls never
+    passes for an exchanged word: every word holds the epoch (upper 32 bits) that
+    the next launch waits for first or second, and the results stay bit for bit
+    those of a fresh workspace."""
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    prob = box(nx, ny, 1, 0, **FIELDS)
+    psi0 = torch.from_numpy(packets.gaussian_packet(prob, 1.0, (1.0, -2.0))).cuda()
+
+    def run(prop):
+        if call == "eigen":
+            ev, bd = prop.eigen(psi0, 100, -1e9, 1e9, 4e9, n_wanted=2)
+            return torch.tensor(np.concatenate([ev, bd]))
+        x = psi0.clone()
+        if call == "async":
+            prop.step_async(x, 0.0, 1e-4, 5)
+            prop.wait()
+        else:
+            prop.step(x, 0.0, 1e-4, 5)
+        return x
+
+    say(f"foreign words {nx}x{ny} ahead {ahead} {call}")
+    prop = Propagator(prob, 6, "fp64", k_eigen=100)
+    ref = run(prop)
+    start = prop.ws_ptr - prop.workspace.data_ptr()
+    words = prop.workspace[start:start + prop.ws_bytes // 8 * 8].view(torch.int64)
+    sums = words[:7680]  # the workspace starts with the words of the sums: 0 or an epoch
+    last = int((sums >> 32).max())
+    assert 0 < last < 2 ** 31 - 2
+    # (asynchronous calls keep their status in the workspace: there only the sums)
+    (sums if call == "async" else words).fill_(((last + ahead) << 32) | 0x3F800000)
+    again = run(prop)
+    prop.close()
+    assert torch.equal(again, ref)
