@@ -875,8 +875,10 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
                                   bd.data(), nullptr, nullptr);
         merge_converged(found, ev.data(), bd.data(), nf, tol);
     };
-    int pending = 0;  // checkpoint fetched but not yet solved
+    int pending = 0;      // checkpoint fetched but not yet solved
+    bool queued = false;  // passes enqueued since the last fetch
     for (int pp = 2; pp <= K1; ++pp) {
+        queued = true;
         const int next = std::min(K1, (pp - 2) / kEigenCheckEvery * kEigenCheckEvery + kEigenCheckEvery + 1);
         if ((pp - 2) % kEigenCheckEvery == 0 && resident(pp, next)) {
             pp = next;
@@ -912,6 +914,7 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
             const bool enough = (int)found.size() >= n_wanted;
             dl_status s = fetch(!on_device && !enough);
             if (s != DL_OK) return s;
+            queued = false;
             if (enough) break;
             if (hs.kstop < pp) break;  // breakdown: the recurrence is over
             const int nw = on_device ? (int)rec.ritz[0] : -1;
@@ -932,9 +935,15 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
         }
     }
     DL_HIP(ctx, hipGetLastError());
+    // the call returns with its work done and its failures reported
+    const bool unread = !queued;
+    if (queued) {
+        const dl_status s = fetch(true);
+        if (s != DL_OK) return s;
+    }
     if (pending > 0) harvest(pending);
     if ((int)found.size() < n_wanted) {
-        const dl_status s = fetch(true);
+        const dl_status s = unread ? fetch(true) : DL_OK;
         if (s != DL_OK) return s;
         const int k = std::min(hs.keff, k_max);
         if (k > 0) harvest(k);
