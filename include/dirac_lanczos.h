@@ -182,8 +182,8 @@ dl_status dirac_lanczos_apply(dl_context *ctx, const void *x, void *y, double t)
  * non-finite reduction stops the remaining steps on the device, and psi then
  * holds the state after the last completed step).  dirac_lanczos_wait
  * synchronises and reports the outcome and the statistics; a failure not yet
- * reported by it is reported (DL_ERR_NONFINITE, the call doing nothing else)
- * by the next synchronous call on the context.  The per-step fields of an
+ * reported by it is reported (DL_ERR_NONFINITE, or DL_ERR_DEVICE for a resident
+ * launch that waited too long, the call doing nothing else) by the next synchronous call on the context.  The per-step fields of an
  * asynchronous call are staged through pinned host buffers the context
  * allocates on first use.
  */
@@ -193,8 +193,9 @@ dl_status dirac_lanczos_step(dl_context *ctx, void *psi, double t0, double dt, i
 /*
  * Wait for the work of the context's asynchronous step calls (stats == NULL
  * in dirac_lanczos_step, _step_lowmem, _step_ktol) and report the last one:
- * DL_OK, or DL_ERR_NONFINITE if a reduction became non-finite (psi then holds
- * the state after the last completed step).  steps_done (HOST, may be NULL)
+ * DL_OK, or DL_ERR_NONFINITE if a reduction became non-finite, or DL_ERR_DEVICE
+ * if a resident launch waited too long (psi then holds the state after the last
+ * completed step).  steps_done (HOST, may be NULL)
  * receives the number of completed steps of the last call.  stats (HOST,
  * n_stats entries, may be NULL with n_stats = 0) receives the statistics of
  * the last call's steps as dirac_lanczos_step would have returned them, for
@@ -495,6 +496,22 @@ dl_status dirac_lanczos_set_launch(dl_context *ctx, int32_t sweep_waves_per_cu, 
 dl_status dirac_lanczos_batch_set_launch(dl_batch *batch, int32_t rows_per_chunk, int32_t *rows_out);
 
 /*
+ * Resident launches (grids of up to about 1.1 million sites: time steps, the
+ * adjoint's steps and the plain eigen mode): one workgroup on up to every
+ * compute unit, which wait for one another inside the launch.  Launches of
+ * several contexts therefore run one after the other, also on different streams
+ * (their sweeps would overlap), and a launch needs the device to itself for as
+ * long as it waits.  seconds (0..3600, default 20): the longest it waits, from
+ * its start; then what is left of the call, and all later calls of the context,
+ * run as sweeps.  Asynchronous steps cannot be continued so: dirac_lanczos_wait
+ * or the next synchronous call reports DL_ERR_DEVICE, with psi after the last
+ * completed step.  seconds = 0: sweeps only, e.g. for many contexts on streams of
+ * their own.  A context whose launch was refused by the runtime also runs sweeps
+ * from then on; this call and dirac_lanczos_set_launch make it try again.
+ */
+dl_status dirac_lanczos_set_wait(dl_context *ctx, double seconds);
+
+/*
  * Kernel timing with HIP events recorded on the context's stream around every
  * launch of dirac_lanczos_step, or by the device's clock inside its resident
  * launches (a diagnostic for roofline measurements; each iteration counts as a
@@ -519,10 +536,11 @@ dl_status dirac_lanczos_timing(dl_context *ctx, int32_t enable, dl_timing *out);
  * tight serving loops, harnesses that forbid allocation): n_steps steps of
  * dirac_lanczos_step for the problem `params`, on hip_stream (NULL: the
  * default stream), without a context or a caller workspace.  The workspace of
- * the step lives in a static device array of 64 MiB that every GPU the
- * library runs on holds until the process ends; the problem must fit it
- * (dirac_lanczos_workspace_bytes(params, DL_MODE_STEP, 0) <= 64 MiB: about
- * 350^2 sites in FP64 or 490^2 in mixed precision at m = 16), otherwise
+ * the step lives in a static device array that every GPU the library runs on
+ * holds until the process ends: 64 MiB, plus 10 MiB for the exchange buffers and
+ * small arrays of resident launches; the problem must fit the 64 MiB
+ * (dirac_lanczos_workspace_bytes(params, DL_MODE_STEP, 0) without its exchange
+ * buffers: about 350^2 sites in FP64 or 490^2 in mixed precision at m = 16), otherwise
  * DL_ERR_WORKSPACE before any device work.  The call allocates nothing on the
  * device or the host.  Calls on one GPU share that array: calls that overlap
  * in time on a GPU (from several threads or streams) race; sequential calls
@@ -531,7 +549,8 @@ dl_status dirac_lanczos_timing(dl_context *ctx, int32_t enable, dl_timing *out);
  * stats != NULL (HOST, n_steps entries): synchronous, statistics and
  * DL_ERR_NONFINITE as for dirac_lanczos_step.  stats == NULL: the work is only
  * enqueued (kernels only, no host copies), and a non-finite reduction is not
- * reported.  Errors: DL_ERR_INVALID, DL_ERR_WORKSPACE, DL_ERR_DEVICE (no
+ * reported; a resident launch that waited too long (dirac_lanczos_set_wait) sets
+ * psi to NaN.  Errors: DL_ERR_INVALID, DL_ERR_WORKSPACE, DL_ERR_DEVICE (no
  * gfx950 device, or a HIP failure); no message is kept.
  */
 dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *psi, double t0, double dt, int32_t n_steps,

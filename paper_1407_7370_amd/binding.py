@@ -31,7 +31,7 @@ EXPORTS = ("dirac_lanczos_workspace_bytes", "dirac_lanczos_init", "dirac_lanczos
            "dirac_lanczos_step_lowmem", "dirac_lanczos_eigen_vectors", "dirac_lanczos_step_ktol",
            "dirac_lanczos_wait", "dirac_lanczos_step_noalloc", "dirac_lanczos_hermite_nodes",
            "dirac_lanczos_hermite_workspace_bytes", "dirac_lanczos_hermite_apply", "dirac_lanczos_hermite_eigen",
-           "dirac_lanczos_hermite_last_error", "dirac_lanczos_ritz")
+           "dirac_lanczos_hermite_last_error", "dirac_lanczos_ritz", "dirac_lanczos_set_wait")
 DL_LOSS_X, DL_LOSS_Y, DL_LOSS_PX, DL_LOSS_PY = 1, 2, 4, 8
 
 
@@ -193,6 +193,8 @@ def load_library():
     I = ctypes.POINTER(ctypes.c_int32)
     lib.dirac_lanczos_set_launch.argtypes = [vp, ctypes.c_int32, I]
     lib.dirac_lanczos_set_launch.restype = ctypes.c_int
+    lib.dirac_lanczos_set_wait.argtypes = [vp, ctypes.c_double]
+    lib.dirac_lanczos_set_wait.restype = ctypes.c_int
     lib.dirac_lanczos_batch_set_launch.argtypes = [vp, ctypes.c_int32, I]
     lib.dirac_lanczos_batch_set_launch.restype = ctypes.c_int
     lib.dirac_lanczos_step_adaptive.argtypes = [vp, vp, ctypes.c_double, ctypes.c_double, ctypes.c_double,
@@ -507,6 +509,11 @@ class Propagator:
         _check(self.lib, self.ctx, self.lib.dirac_lanczos_set_launch(self.ctx, int(sweep_waves_per_cu),
                                                                      ctypes.byref(w)))
         return int(w.value)
+
+    def set_wait(self, seconds: float):
+        """Longest wait inside a resident launch (20 s by default); what is left of
+        a call after it, and later calls, run as sweeps.  0: sweeps only."""
+        _check(self.lib, self.ctx, self.lib.dirac_lanczos_set_wait(self.ctx, float(seconds)))
 
     def timing(self, enable: bool):
         """Start (True) or stop (False) event timing; returns the accumulated

@@ -246,11 +246,10 @@ size_t dirac_lanczos_adjoint_workspace_bytes(const dl_params *params, int32_t n_
     return adj_plan(*params, n_steps, ckpt_every).total;
 }
 
-dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, double dt, int32_t n_steps,
-                                int32_t ckpt_every, int32_t loss_kind, void *adj_ws, size_t adj_bytes,
-                                double *loss, double *grad)
+static dl_status adjoint_run(dl_context *ctx, const void *psi0_v, double t0, double dt, int32_t n_steps,
+                             int32_t ckpt_every, int32_t loss_kind, void *adj_ws, size_t adj_bytes, double *loss,
+                             double *grad)
 {
-    if (!ctx) return DL_ERR_INVALID;
     if (!psi0_v || !loss || !grad) return ctx->fail(DL_ERR_INVALID, "psi0, loss and grad must be non-NULL");
     if (loss_kind < 1 || loss_kind > 15) return ctx->fail(DL_ERR_INVALID, "loss_kind must be in 1..15");
     if (!(dt > 0.0) || !std::isfinite(dt) || !std::isfinite(t0))
@@ -554,4 +553,14 @@ dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, 
     *loss = hobs[5];
     std::copy(gsum.begin(), gsum.end(), grad);
     return DL_OK;
+}
+
+dl_status dirac_lanczos_adjoint(dl_context *ctx, const void *psi0_v, double t0, double dt, int32_t n_steps,
+                                int32_t ckpt_every, int32_t loss_kind, void *adj_ws, size_t adj_bytes,
+                                double *loss, double *grad)
+{
+    if (!ctx) return DL_ERR_INVALID;
+    return with_sweeps_after_timeout(ctx, [&] {
+        return adjoint_run(ctx, psi0_v, t0, dt, n_steps, ckpt_every, loss_kind, adj_ws, adj_bytes, loss, grad);
+    });
 }

@@ -138,6 +138,9 @@ struct dl_context {
     bool combine_wide = false;       // recombination in the wide form (more sites per thread)
     int combine_blocks_wide = 1024;  // its workgroups
     dl::ResidentTiles resident{};    // tiles of the resident steps (rows = 0: not used)
+    // longest wait inside a resident launch, in 100 MHz ticks (dirac_lanczos_set_wait)
+    unsigned long long wait_ticks = 20ull * 100000000ull;
+    bool timed_out = false;  // a resident launch gave up (the context runs sweeps since)
     int sweep_waves = 8;  // waves per compute unit of the sweeps (launch shape)
     std::vector<double> host_fields;
     std::vector<dl::StepStat> host_stats;
@@ -157,10 +160,15 @@ struct dl_context {
         hipError_t e = hipMemcpyAsync(tk, ws + L.ticks, sizeof(tk), hipMemcpyDeviceToHost, stream);
         return e != hipSuccess ? e : hipStreamSynchronize(stream);
     }
-    // the failure a non-zero Scalars::status stands for
+    // the failure a non-zero Scalars::status stands for; after a time-out of a
+    // resident launch the context runs sweeps
     dl_status status_fail(int status, const std::string &msg)
     {
-        if (status == dl::kStatusTimeout) return fail(DL_ERR_DEVICE, "a resident step waited too long: " + msg);
+        if (status == dl::kStatusTimeout) {
+            resident = dl::ResidentTiles{};
+            timed_out = true;
+            return fail(DL_ERR_DEVICE, "a resident launch waited too long for its workgroups: " + msg);
+        }
         return fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction " + msg);
     }
     // asynchronous steps (stats == NULL): two pinned host buffers stage the
@@ -305,8 +313,19 @@ void configure_launch(dl_context *ctx);
 // synchronous entry point that resets the scalars calls it first.
 dl_status take_async_failure(dl_context *ctx);
 unsigned long long *ticks_of(const dl_context *ctx);
-// Scalars and exchange buffers as a call's first launch needs them (see k_reset).
-void reset_call(dl_context *ctx, int keep_status = 0, int kmin = 0, int kmax = 0, double ktol = 0.0);
+// call(), and if one of its resident launches waited too long (the device was not
+// free for all its workgroups at once) call() again, as sweeps.
+template <class F>
+dl_status with_sweeps_after_timeout(dl_context *ctx, F &&call)
+{
+    ctx->timed_out = false;
+    const dl_status s = call();
+    return ctx->timed_out ? call() : s;
+}
+// Scalars and exchange buffers as a call's first launch, or the first after
+// `steps_done` steps of it, needs them (see k_reset).
+void reset_call(dl_context *ctx, int steps_done = 0, int keep_status = 0, int kmin = 0, int kmax = 0,
+                double ktol = 0.0);
 
 // Eigen mode with full reorthogonalisation (eigen.cpp); vecs (device, may be
 // NULL) receives the Ritz vectors of the reported values.

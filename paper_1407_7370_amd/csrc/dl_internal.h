@@ -206,6 +206,7 @@ struct ResidentArgs {
     size_t keep_step, keep_alpha, keep_gamma;
     unsigned long long *red, *halo;  // exchange buffers
     uint32_t epoch;                  // the epoch before the launch's first (set by the launch functions)
+    unsigned long long wait_ticks;   // longest wait of a workgroup for the others, from its start (100 MHz ticks)
     unsigned long long *ticks;       // per kernel class, the launch's 100 MHz ticks are added (timing), or NULL
     __host__ __device__ double2 *state_in(int s) const
     {
@@ -299,13 +300,15 @@ void launch_combine(const CombArgs &a, bool mixed, bool wide, int nblocks, hipSt
 void launch_apply(const Op &op, const Tiles &t, const double2 *x, double2 *y, double gxh,
                   double gyh, hipStream_t st);
 void launch_reset(Scalars *sc, hipStream_t st);
-// Reset at the start of a step call (see k_reset): keep_status for
+// Reset at the start of a step call or after some of its steps (see k_reset): keep_status for
 // asynchronous calls, the adaptive-dimension parameters (ktol = 0: off), the
 // exchange buffers to clear (16-byte multiples, or none).
-void launch_reset_call(Scalars *sc, int keep_status, int kmin, int kmax, double ktol, void *comm, size_t comm_bytes,
-                       hipStream_t st);
-// psi <- state (n complex128 values) when sc->steps_done is odd.
-void launch_finish_copy(const Scalars *sc, const double2 *state, double2 *psi, size_t n, int cus, hipStream_t st);
+void launch_reset_call(Scalars *sc, int steps_done, int keep_status, int kmin, int kmax, double ktol, void *comm,
+                       size_t comm_bytes, hipStream_t st);
+// psi <- state (n complex128 values) when sc->steps_done is odd; mark: psi <- NaN
+// after a resident launch that waited too long (callers that read no status).
+void launch_finish_copy(const Scalars *sc, const double2 *state, double2 *psi, size_t n, int cus, bool mark,
+                        hipStream_t st);
 
 // ---------------------------------------------------------------------------
 // Batches of independent packets (grids of different sizes and fields, one

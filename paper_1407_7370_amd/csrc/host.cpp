@@ -372,6 +372,7 @@ dl_status run_resident(dl_context *ctx, const Engine &e, const dl::Op &op, const
     a.keep_gamma = r.keep_gamma;
     a.red = reinterpret_cast<unsigned long long *>(ws + L.comm);
     a.halo = reinterpret_cast<unsigned long long *>(ws + L.comm + dl::kCommRed);
+    a.wait_ticks = ctx->wait_ticks;
     a.ticks = ctx->timing ? ticks_of(ctx) : nullptr;
     for (int i = 0; i < n; i += dl::kResidentSteps) {
         a.n_steps = std::min(dl::kResidentSteps, n - i);
@@ -407,10 +408,10 @@ unsigned long long *ticks_of(const dl_context *ctx)
     return reinterpret_cast<unsigned long long *>(ctx->ws + ctx->L.ticks);
 }
 
-void reset_call(dl_context *ctx, int keep_status, int kmin, int kmax, double ktol)
+void reset_call(dl_context *ctx, int steps_done, int keep_status, int kmin, int kmax, double ktol)
 {
-    dl::launch_reset_call(ctx->sc(), keep_status, kmin, kmax, ktol, ctx->ws + ctx->L.comm, ctx->resident.comm(),
-                          ctx->stream);
+    dl::launch_reset_call(ctx->sc(), steps_done, keep_status, kmin, kmax, ktol, ctx->ws + ctx->L.comm,
+                          ctx->resident.comm(), ctx->stream);
 }
 
 dl_status take_async_failure(dl_context *ctx)
@@ -464,6 +465,14 @@ int default_sweep_waves(const dl_params &p, int cus)
     return (int)std::max(2L, std::min<long>(w, DL_RECUR_WAVES_PER_CU));
 }
 
+// Tiles of the resident launches (rows = 0: none); the workspace holds the exchange
+// buffers when the grid fits kResidentWgs.
+dl::ResidentTiles resident_of(const dl_context *ctx)
+{
+    const dl::ResidentTiles t = dl::resident_tiles(ctx->p.nx, ctx->p.ny, dl::kResidentWgs);
+    return t.ntx * t.nty > ctx->cus || ctx->wait_ticks == 0 ? dl::ResidentTiles{} : t;
+}
+
 void set_tiles(dl_context *ctx, int cap)
 {
     const dl_params &p = ctx->p;
@@ -488,9 +497,7 @@ void set_tiles(dl_context *ctx, int cap)
     ctx->combine_blocks = dl::combine_grid(vec_elems(p) / 2, mixed, ctx->cus, !mixed);
     ctx->combine_wide = dl::combine_wide(vec_elems(p) / 2, mixed, ctx->cus);
     ctx->combine_blocks_wide = dl::combine_grid(vec_elems(p) / 2, mixed, ctx->cus, ctx->combine_wide);
-    // (the workspace holds the exchange buffers when the grid fits kResidentWgs)
-    ctx->resident = dl::resident_tiles(p.nx, p.ny, dl::kResidentWgs);
-    if (ctx->resident.ntx * ctx->resident.nty > ctx->cus) ctx->resident = dl::ResidentTiles{};
+    ctx->resident = resident_of(ctx);
 }
 
 }  // namespace
@@ -669,14 +676,14 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
 
     // adaptive dimension (ktol > 0): the first step runs m iterations, later
     // ones the dimension the previous step predicted
-    reset_call(ctx, async ? 1 : 0, ktol > 0.0 ? kmin : 0, ktol > 0.0 ? m : 0, ktol > 0.0 ? ktol : 0.0);
+    reset_call(ctx, 0, async ? 1 : 0, ktol > 0.0 ? kmin : 0, ktol > 0.0 ? m : 0, ktol > 0.0 ? ktol : 0.0);
     DL_HIP(ctx, hipGetLastError());
     double cum = 0.0;
-    int completed = 0, status = 0;
+    int completed = 0;
     bool aborted = false;
     ctx->host_stats.resize(kChunk);
-    for (int s0 = 0; s0 < n_steps && !aborted; s0 += kChunk) {
-        const int nc = std::min(kChunk, n_steps - s0);
+    for (int s0 = 0, nc; s0 < n_steps && !aborted; s0 += nc) {
+        nc = std::min(kChunk, n_steps - s0);
         const dl_status sf = stage_fields(ctx, async, t0, dt, s0, nc, fields);
         if (sf != DL_OK) return sf;
         int first = 0;
@@ -731,12 +738,18 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
             }
         }
         completed = hs.steps_done;
-        status = hs.status;
-        if (status != 0) aborted = true;
+        aborted = hs.status != 0;
+        if (hs.status == dl::kStatusTimeout) {
+            // the state after the completed steps is whole: the others as sweeps
+            ctx->resident = dl::ResidentTiles{};
+            reset_call(ctx, completed);
+            nc = completed - s0;
+            aborted = false;
+        }
     }
     if (async) {
         // the state after the completed steps is copied to psi on the device
-        dl::launch_finish_copy(sc, state, psi, n, ctx->cus, st);
+        dl::launch_finish_copy(sc, state, psi, n, ctx->cus, false, st);
         DL_HIP(ctx, hipGetLastError());
         ctx->async_pending = true;
         return DL_OK;
@@ -751,7 +764,9 @@ static dl_status run_steps(dl_context *ctx, void *psi_v, double t0, double dt, i
         DL_HIP(ctx, hipMemcpyAsync(psi, state, n * 16, hipMemcpyDeviceToDevice, st));
         DL_HIP(ctx, hipStreamSynchronize(st));
     }
-    if (aborted) return ctx->status_fail(status, "after " + std::to_string(completed) + " completed steps");
+    if (aborted)
+        return ctx->fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction after " +
+                                               std::to_string(completed) + " completed steps");
     return DL_OK;
 }
 
@@ -777,18 +792,9 @@ dl_status dirac_lanczos_step_ktol(dl_context *ctx, void *psi, double t0, double 
     return run_steps(ctx, psi, t0, dt, n_steps, stats, false, tol, k_min);
 }
 
-dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, int32_t reorth,
-                              double e_lo, double e_hi, double tol, int32_t n_wanted, double *evals,
-                              double *bounds, int32_t *n_found)
+static dl_status eigen_plain(dl_context *ctx, const void *psi0, int32_t k_max, double e_lo, double e_hi, double tol,
+                             int32_t n_wanted, double *evals, double *bounds, int32_t *n_found)
 {
-    if (!ctx) return DL_ERR_INVALID;
-    if (!psi0 || !evals || !bounds || !n_found || n_wanted < 1 || k_max < 1 || !(tol >= 0.0) ||
-        !(e_hi >= e_lo))
-        return ctx->fail(DL_ERR_INVALID, "invalid eigen arguments");
-    *n_found = 0;
-    const dl_status pend = take_async_failure(ctx);
-    if (pend != DL_OK) return pend;
-    if (reorth) return eigen_reorth(ctx, psi0, k_max, e_lo, e_hi, tol, n_wanted, evals, bounds, n_found, nullptr);
     const dl_params &p = ctx->p;
     const Layout E = plan(p, DL_MODE_EIGEN, k_max);
     if (ctx->ws_bytes < E.total)
@@ -845,6 +851,7 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
     dl::ResidentArgs ra{};
     ra.op = op;
     ra.sc = sc;
+    ra.wait_ticks = ctx->wait_ticks;
     ra.red = reinterpret_cast<unsigned long long *>(ws + E.comm);
     ra.halo = reinterpret_cast<unsigned long long *>(ws + E.comm + dl::kCommRed);
     ra.eig.alpha = alpha;
@@ -957,6 +964,22 @@ dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, 
     return DL_OK;
 }
 
+dl_status dirac_lanczos_eigen(dl_context *ctx, const void *psi0, int32_t k_max, int32_t reorth,
+                              double e_lo, double e_hi, double tol, int32_t n_wanted, double *evals,
+                              double *bounds, int32_t *n_found)
+{
+    if (!ctx) return DL_ERR_INVALID;
+    if (!psi0 || !evals || !bounds || !n_found || n_wanted < 1 || k_max < 1 || !(tol >= 0.0) ||
+        !(e_hi >= e_lo))
+        return ctx->fail(DL_ERR_INVALID, "invalid eigen arguments");
+    *n_found = 0;
+    const dl_status pend = take_async_failure(ctx);
+    if (pend != DL_OK) return pend;
+    if (reorth) return eigen_reorth(ctx, psi0, k_max, e_lo, e_hi, tol, n_wanted, evals, bounds, n_found, nullptr);
+    return with_sweeps_after_timeout(
+        ctx, [&] { return eigen_plain(ctx, psi0, k_max, e_lo, e_hi, tol, n_wanted, evals, bounds, n_found); });
+}
+
 dl_status dirac_lanczos_wait(dl_context *ctx, dl_step_stat *stats, int32_t n_stats, int32_t *steps_done)
 {
     if (!ctx) return DL_ERR_INVALID;
@@ -1008,6 +1031,15 @@ dl_status dirac_lanczos_set_launch(dl_context *ctx, int32_t sweep_waves_per_cu, 
         return ctx->fail(DL_ERR_INVALID, "sweep_waves_per_cu must be in 0..64");
     set_tiles(ctx, sweep_waves_per_cu);
     if (waves_out) *waves_out = ctx->sweep_waves;
+    return DL_OK;
+}
+
+dl_status dirac_lanczos_set_wait(dl_context *ctx, double seconds)
+{
+    if (!ctx) return DL_ERR_INVALID;
+    if (!(seconds >= 0.0) || seconds > 3600.0) return ctx->fail(DL_ERR_INVALID, "seconds must be in 0..3600");
+    ctx->wait_ticks = seconds > 0.0 ? std::max(1ull, (unsigned long long)(seconds * 1e8)) : 0ull;
+    ctx->resident = resident_of(ctx);
     return DL_OK;
 }
 

@@ -171,22 +171,23 @@ void launch_apply(const Op &op, const Tiles &t, const double2 *x, double2 *y, do
     hipLaunchKernelGGL(k_apply, dim3(t.nblocks), dim3(kBlock), 0, st, op, t, x, y, gxh, gyh);
 }
 
-void launch_reset(Scalars *sc, hipStream_t st) { launch_reset_call(sc, 0, 0, 0, 0.0, nullptr, 0, st); }
+void launch_reset(Scalars *sc, hipStream_t st) { launch_reset_call(sc, 0, 0, 0, 0, 0.0, nullptr, 0, st); }
 
-void launch_reset_call(Scalars *sc, int keep_status, int kmin, int kmax, double ktol, void *comm, size_t comm_bytes,
-                       hipStream_t st)
+void launch_reset_call(Scalars *sc, int steps_done, int keep_status, int kmin, int kmax, double ktol, void *comm,
+                       size_t comm_bytes, hipStream_t st)
 {
     const size_t words = comm_bytes / sizeof(uint4);
     const size_t blocks = std::max<size_t>(1, std::min<size_t>(1024, words / kBlock));
-    hipLaunchKernelGGL(k_reset, dim3((unsigned)blocks), dim3(kBlock), 0, st, sc, keep_status, kmin, kmax, ktol,
+    hipLaunchKernelGGL(k_reset, dim3((unsigned)blocks), dim3(kBlock), 0, st, sc, steps_done, keep_status, kmin, kmax, ktol,
                        static_cast<uint4 *>(comm), words);
 }
 
-void launch_finish_copy(const Scalars *sc, const double2 *state, double2 *psi, size_t n, int cus, hipStream_t st)
+void launch_finish_copy(const Scalars *sc, const double2 *state, double2 *psi, size_t n, int cus, bool mark,
+                        hipStream_t st)
 {
     const size_t blocks = std::min<size_t>((size_t)4 * cus, (n + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_finish_copy, dim3((unsigned)std::max<size_t>(blocks, 1)), dim3(kBlock), 0, st, sc, state,
-                       psi, n);
+                       psi, n, (int)mark);
 }
 
 }  // namespace dl

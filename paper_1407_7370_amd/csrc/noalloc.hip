@@ -117,10 +117,10 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
     reset_call(&ctx);
     if (hipGetLastError() != hipSuccess) return DL_ERR_DEVICE;
     double cum = 0.0;
-    int completed = 0, status = 0;
+    int completed = 0;
     bool aborted = false;
-    for (int s0 = 0; s0 < n_steps && !aborted; s0 += kRound) {
-        const int nc = std::min(kRound, n_steps - s0);
+    for (int s0 = 0, nc; s0 < n_steps && !aborted; s0 += nc) {
+        nc = std::min(kRound, n_steps - s0);
         FieldBlock fb;
         for (int i = 0; i < nc; ++i) {
             double a[2];
@@ -169,8 +169,14 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
             }
         }
         completed = hsc.steps_done;
-        status = hsc.status;
-        aborted = status != 0;
+        aborted = hsc.status != 0;
+        if (hsc.status == dl::kStatusTimeout) {
+            // the state after the completed steps is whole: the others as sweeps
+            ctx.resident = dl::ResidentTiles{};
+            reset_call(&ctx, completed);
+            nc = completed - s0;
+            aborted = false;
+        }
     }
     if (stats && aborted)
         for (int i = completed; i < n_steps; ++i) {
@@ -178,9 +184,8 @@ extern "C" dl_status dirac_lanczos_step_noalloc(const dl_params *params, void *p
             stats[i].err_est = stats[i].cum_bound = stats[i].norm2 = stats[i].round_bound = 0.0;
         }
     // the state after the completed steps is moved to psi on the device
-    dl::launch_finish_copy(sc, state, psi, n, cus, st);
+    dl::launch_finish_copy(sc, state, psi, n, cus, !stats, st);
     if (hipGetLastError() != hipSuccess) return DL_ERR_DEVICE;
     if (stats && hipStreamSynchronize(st) != hipSuccess) return DL_ERR_DEVICE;
-    if (aborted) return status == dl::kStatusTimeout ? DL_ERR_DEVICE : DL_ERR_NONFINITE;
-    return DL_OK;
+    return aborted ? DL_ERR_NONFINITE : DL_OK;
 }

@@ -33,7 +33,8 @@
 // (512^2: 12.3 us an iteration, of which 6 us for the sums).
 //
 // All workgroups must be resident at once: the launch is cooperative.  Every
-// wait is bounded in time (kWaitTicks), after which the call fails.
+// wait is bounded in time (ResidentArgs::wait_ticks from the launch's start), after
+// which the workgroups leave and the host runs what is left as sweeps.
 //
 // What bounds it: the latency chain of an iteration (partials and border
 // through memory, workgroup barriers, the tile's arithmetic: 3.2 us at 64^2, 5.9
@@ -63,7 +64,6 @@ constexpr int kCopies = 8;    // copies of the groups' sums
 static_assert(kLeaders * kGroup >= kResidentWgs, "every workgroup has a group");
 static_assert(kCommRed >= sizeof(unsigned long long) * 2 * 10 * (kLeaders * kGroup + kLeaders * kCopies),
               "the exchange buffers hold the sums");
-constexpr unsigned long long kWaitTicks = 20ull * 100000000ull;  // 20 s of the 100 MHz clock
 
 __device__ __forceinline__ void put_word(unsigned long long *p, uint32_t payload, uint32_t epoch)
 {
@@ -367,9 +367,11 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
         }
     };
     // words q = 0 .. 2 nv - 1 of lane's slot (stride apart), once they are of the current
-    // epoch, as nv doubles; lanes that are not `on` get zeros
-    auto poll_sums = [&](const unsigned long long *p, size_t stride, bool on, auto nvc, double(&v)[5]) {
+    // epoch, as nv doubles; lanes that are not `on` get zeros.  False on a lane
+    // whose wait ran out of time (its values are not sums)
+    auto poll_sums = [&](const unsigned long long *p, size_t stride, bool on, auto nvc, double(&v)[5]) -> bool {
         constexpr int nv = decltype(nvc)::value;
+        bool whole = true;
         unsigned long long w[2 * nv];
 #pragma unroll
         for (int q = 0; q < 2 * nv; ++q) w[q] = 0;
@@ -381,13 +383,15 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 #pragma unroll
                 for (int q = 0; q < 2 * nv; ++q) ok &= (uint32_t)(w[q] >> 32) == epoch;
                 if (ok) break;
-                if (wall_clock64() - started > kWaitTicks) {
+                if (wall_clock64() - started > a.wait_ticks) {
                     sh.dead = 1;
+                    whole = false;
                     break;
                 }
             }
 #pragma unroll
         for (int q = 0; q < nv; ++q) v[q] = join(w[2 * q], w[2 * q + 1]);
+        return whole;
     };
     // the totals of all workgroups (and, with border, the border sites of the
     // current vector into LDS); false when a wait ran out of time
@@ -403,12 +407,14 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                 for (int q = 0; q < nv; ++q) v[q] = lanes_sum(v[q]);
             } else {
                 if (wg < kLeaders) {  // leads group wg
-                    poll_sums(red + par * red_buf + (size_t)wg * 10 * kGroup + lane, kGroup,
-                              lane < kGroup && wg + kLeaders * lane < nwg, nvc, v);
+                    const bool whole = poll_sums(red + par * red_buf + (size_t)wg * 10 * kGroup + lane, kGroup,
+                                                 lane < kGroup && wg + kLeaders * lane < nwg, nvc, v);
+                    // (a sum that is not whole is not sent: the others' waits end too)
+                    const bool send = lane < kCopies && __all(whole);
 #pragma unroll
                     for (int q = 0; q < nv; ++q) {
                         v[q] = row_sum(v[q]);
-                        if (lane < kCopies) {
+                        if (send) {
                             unsigned long long *const o = red2 + par * red2_buf + (lane * 10 + 2 * q) * kLeaders + wg;
                             put_word(o, (uint32_t)__double2loint(v[q]), epoch);
                             put_word(o + kLeaders, (uint32_t)__double2hiint(v[q]), epoch);
@@ -432,7 +438,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 #pragma unroll
                 for (int q = 0; q < NW; ++q) ok &= (uint32_t)(h[q] >> 32) == epoch;
                 if (ok) break;
-                if (wall_clock64() - started > kWaitTicks) {
+                if (wall_clock64() - started > a.wait_ticks) {
                     sh.dead = 1;
                     break;
                 }
@@ -661,7 +667,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                     a.eig.o2[g + 1] = make_double2(R[k].r1, R[k].i1);
                 }
         }
-        if (timeout && wg == 0 && t == 0) {
+        if (timeout && t == 0) {  // (any workgroup: its tile of the outputs is missing)
             sc->status = kStatusTimeout;
             sc->kstop = -1;
         }

@@ -1833,14 +1833,14 @@ __global__ __launch_bounds__(kBlock) void k_apply(Op op, Tiles t, const double2 
 // (ktol = 0: off).  comm: the exchange buffers of resident launches (n 16-byte
 // words), cleared so that nothing else that was in the memory (another context's
 // vectors, epochs of long ago) can pass for a word of the call's launches.
-__global__ __launch_bounds__(kBlock) void k_reset(Scalars *sc, int keep_status, int kmin, int kmax, double ktol,
+__global__ __launch_bounds__(kBlock) void k_reset(Scalars *sc, int steps_done, int keep_status, int kmin, int kmax, double ktol,
                                                   uint4 *comm, size_t n)
 {
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock)
         comm[i] = make_uint4(0u, 0u, 0u, 0u);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (!keep_status) sc->status = 0;
-        sc->steps_done = 0;
+        sc->steps_done = steps_done;
         sc->ticket = 0u;
         sc->kstop = sc->status != 0 ? -1 : 0;
         sc->keff = 0;
@@ -1857,10 +1857,18 @@ __global__ __launch_bounds__(kBlock) void k_reset(Scalars *sc, int keep_status, 
 
 // End of an asynchronous call: the state after the completed steps is in
 // `state` when their number is odd (the steps alternate between the caller's
-// psi and the workspace); copy it to psi there, do nothing otherwise.
+// psi and the workspace); copy it to psi there, do nothing otherwise.  mark: a
+// time-out of a resident launch, which the caller does not read, sets psi to NaN.
 __global__ __launch_bounds__(kBlock) void k_finish_copy(const Scalars *sc, const double2 *__restrict__ state,
-                                                        double2 *__restrict__ psi, size_t n)
+                                                        double2 *__restrict__ psi, size_t n, int mark)
 {
+    const bool lost = mark && sc->status == kStatusTimeout;
+    if (lost) {
+        const double nan = __builtin_nan("");
+        for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock)
+            psi[i] = make_double2(nan, nan);
+        return;
+    }
     if ((sc->steps_done & 1) == 0) return;
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock)
         psi[i] = state[i];

@@ -224,3 +224,63 @@ def test_foreign_words_in_the_workspace(torch_cuda, nx, ny, ahead, call):
     again = run(prop)
     prop.close()
     assert torch.equal(again, ref)
+
+
+def test_wait_limit_goes_on_in_sweeps(torch_cuda):
+    """A resident launch whose workgroups wait longer than the limit (here one tick,
+    so no step of it completes) leaves the rest of the call, and later calls, to
+    sweeps, with the bits of a context that runs sweeps only; an asynchronous call
+    reports it.  A new limit brings the resident launches back."""
+    from paper_1407_7370_amd import binding
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    prob = box(400, 390, 1, 0, pulse_kind=2, t_pulse=0.05, coef=np.array([10.0, -5.0, 3.0, 8.0]), **FIELDS)
+    psi0 = torch.from_numpy(packets.gaussian_packet(prob, 1.0, (1.0, -2.0))).cuda()
+    n, dt, k = 5, 1e-4, 130
+
+    def run(prop):
+        x = psi0.clone()
+        st = prop.step(x, 0.0, dt, n)
+        ev, bd = prop.eigen(psi0, k, -1e9, 1e9, 4e9, n_wanted=2)
+        loss, grad = prop.adjoint(psi0, 0.0, dt, 7, 3, 9)
+        return x, st, ev, bd, loss, grad
+
+    def same(a, b):
+        assert torch.equal(a[0], b[0])
+        for key in ("k_eff", "err_est", "cum_bound", "norm2"):
+            assert np.array_equal(a[1][key], b[1][key]), key
+        assert all(np.array_equal(p, q) for p, q in zip(a[2:], b[2:]))
+
+    prop = Propagator(prob, 6, "fp64", k_eigen=k)
+    say("wait limit: resident")
+    resident = run(prop)
+    say("wait limit: sweeps only")
+    prop.set_wait(0.0)
+    sweeps = run(prop)
+    assert not torch.equal(sweeps[0], resident[0])  # (another order of the sums)
+    calls = [lambda: prop.step(psi0.clone(), 0.0, dt, n), lambda: prop.eigen(psi0, k, -1e9, 1e9, 4e9, n_wanted=2),
+             lambda: prop.adjoint(psi0, 0.0, dt, 7, 3, 9)]
+    for i, call in enumerate(calls):
+        say(f"wait limit: one tick, call {i}")
+        prop.set_wait(1e-8)
+        call()  # the context runs sweeps after this
+        same(run(prop), sweeps)
+    prop.set_wait(1e-8)
+    same(run(prop), sweeps)
+    say("wait limit: one tick, asynchronous")
+    prop.set_wait(1e-8)
+    x = psi0.clone()
+    prop.step_async(x, 0.0, dt, n)
+    with pytest.raises(binding.DlError) as ei:
+        prop.wait()
+    assert ei.value.status == binding.DL_ERR_DEVICE
+    assert torch.equal(x, psi0)
+    same(run(prop), sweeps)
+    say("wait limit: resident again")
+    prop.set_wait(20.0)
+    same(run(prop), resident)
+    for bad in (-1.0, float("nan"), 1e9):
+        with pytest.raises(binding.DlError) as ei:
+            prop.set_wait(bad)
+        assert ei.value.status == binding.DL_ERR_INVALID
+    prop.close()
