@@ -1048,7 +1048,8 @@ dl_status dirac_lanczos_timing(dl_context *ctx, int32_t enable, dl_timing *out)
     if (!ctx) return DL_ERR_INVALID;
     DL_HIP(ctx, ctx->harvest());
     unsigned long long tk[5] = {0, 0, 0, 0, 0};
-    if (ctx->resident.rows > 0 && (ctx->timing || enable)) DL_HIP(ctx, ctx->read_ticks(tk));
+    // (also when the context runs sweeps by now: earlier resident steps count)
+    if (ctx->timing || enable) DL_HIP(ctx, ctx->read_ticks(tk));
     if (out) {
         for (int i = 0; i < 5; ++i) {
             out->launches[i] = ctx->t_launches[i];

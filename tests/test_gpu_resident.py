@@ -3,6 +3,8 @@ chip's LDS) where they can go wrong: the smallest grids, tiles of unequal size,
 every number of rows per thread, both tile buffer schemes, periodic images that
 are the tile itself, more steps than one launch takes, several contexts and
 streams at once."""
+import time
+
 import numpy as np
 import pytest
 
@@ -284,3 +286,32 @@ def test_wait_limit_goes_on_in_sweeps(torch_cuda):
             prop.set_wait(bad)
         assert ei.value.status == binding.DL_ERR_INVALID
     prop.close()
+
+
+def test_timing_across_the_end_of_resident_steps(torch_cuda):
+    """The times of resident steps are kept when the context goes over to sweeps
+    while timing is on."""
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    prob = box(400, 390, 1, 0, **FIELDS)
+    x = torch.from_numpy(packets.gaussian_packet(prob, 1.0, (1.0, -2.0))).cuda()
+    prop = Propagator(prob, 9, "fp64")
+    say("timing across the end of resident steps")
+    prop.step(x, 0.0, 1e-4, 2)
+    prop.timing(True)
+    prop.step(x, 0.0, 1e-4, 50)
+    resident = {k: ms for k, (_, ms) in prop.timing(False).items()}
+    prop.timing(True)
+    t0 = time.perf_counter()
+    prop.step(x, 0.0, 1e-4, 50)
+    prop.set_wait(0.0)
+    prop.step(x, 0.0, 1e-4, 1)
+    wall = 1e3 * (time.perf_counter() - t0)
+    both = prop.timing(False)
+    prop.close()
+    print(resident, both, wall, flush=True)
+    assert sum(resident.values()) > 0.5
+    # the same fifty resident steps and a step of sweeps, within the wall time
+    assert sum(ms for _, ms in both.values()) <= 1.05 * wall
+    assert sum(ms for _, ms in both.values()) >= 0.5 * sum(resident.values())
+    assert sum(n for n, _ in both.values()) == 51 * (9 + 2)
