@@ -134,6 +134,7 @@ struct ResidentShared {
     double coef[2 * (kMaxM + 2)];
     double wre[kMaxM], wim[kMaxM];
     double cabs;
+    unsigned long long deadline;  // of this workgroup's waits
     int dead, scratch;
 };
 
@@ -367,11 +368,9 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
         }
     };
     // words q = 0 .. 2 nv - 1 of lane's slot (stride apart), once they are of the current
-    // epoch, as nv doubles; lanes that are not `on` get zeros.  False on a lane
-    // whose wait ran out of time (its values are not sums)
-    auto poll_sums = [&](const unsigned long long *p, size_t stride, bool on, auto nvc, double(&v)[5]) -> bool {
+    // epoch, as nv doubles; lanes that are not `on` get zeros
+    auto poll_sums = [&](const unsigned long long *p, size_t stride, bool on, auto nvc, double(&v)[5]) {
         constexpr int nv = decltype(nvc)::value;
-        bool whole = true;
         unsigned long long w[2 * nv];
 #pragma unroll
         for (int q = 0; q < 2 * nv; ++q) w[q] = 0;
@@ -383,15 +382,13 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 #pragma unroll
                 for (int q = 0; q < 2 * nv; ++q) ok &= (uint32_t)(w[q] >> 32) == epoch;
                 if (ok) break;
-                if (wall_clock64() - started > a.wait_ticks) {
+                if (wall_clock64() > sh.deadline) {
                     sh.dead = 1;
-                    whole = false;
                     break;
                 }
             }
 #pragma unroll
         for (int q = 0; q < nv; ++q) v[q] = join(w[2 * q], w[2 * q + 1]);
-        return whole;
     };
     // the totals of all workgroups (and, with border, the border sites of the
     // current vector into LDS); false when a wait ran out of time
@@ -407,10 +404,11 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                 for (int q = 0; q < nv; ++q) v[q] = lanes_sum(v[q]);
             } else {
                 if (wg < kLeaders) {  // leads group wg
-                    const bool whole = poll_sums(red + par * red_buf + (size_t)wg * 10 * kGroup + lane, kGroup,
-                                                 lane < kGroup && wg + kLeaders * lane < nwg, nvc, v);
-                    // (a sum that is not whole is not sent: the others' waits end too)
-                    const bool send = lane < kCopies && __all(whole);
+                    poll_sums(red + par * red_buf + (size_t)wg * 10 * kGroup + lane, kGroup,
+                              lane < kGroup && wg + kLeaders * lane < nwg, nvc, v);
+                    // (after a wait that ran out of time the sum is not whole and is
+                    // not sent, so that the others' waits end too)
+                    const bool send = lane < kCopies && sh.dead == 0;
 #pragma unroll
                     for (int q = 0; q < nv; ++q) {
                         v[q] = row_sum(v[q]);
@@ -438,7 +436,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 #pragma unroll
                 for (int q = 0; q < NW; ++q) ok &= (uint32_t)(h[q] >> 32) == epoch;
                 if (ok) break;
-                if (wall_clock64() - started > a.wait_ticks) {
+                if (wall_clock64() > sh.deadline) {
                     sh.dead = 1;
                     break;
                 }
@@ -587,7 +585,10 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 
     // zero the tile (sites outside a Dirichlet domain stay zero), then psi
     for (int s = t; s < tile_words; s += kRBlock) tile[s] = make_double2(0.0, 0.0);
-    if (t == 0) sh.dead = 0;
+    if (t == 0) {
+        sh.dead = 0;
+        sh.deadline = started + a.wait_ticks;
+    }
     __syncthreads();
     const double2 *in = EIG ? a.eig.u1 : a.state_in(0);
     const bool paired = EIG && a.eig.p0 > 2;  // u_1 is the start vector, in planes
@@ -604,6 +605,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
     load_border(in, paired);
     __syncthreads();
 
+    // ticks per class since the last lap, by the first thread
     unsigned long long clk[5] = {0, 0, 0, 0, 0}, mark = started;
     auto lap = [&](int cls) {
         if (!a.ticks) return;
