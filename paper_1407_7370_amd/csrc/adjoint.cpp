@@ -28,10 +28,12 @@
 // is still resident from the forward pass).  Per-step records (contraction,
 // both tridiagonal chains, shifts, k_eff) are written by the device and read
 // once per segment, so the host never waits inside a segment.  Grids that take
-// resident steps run a whole segment forward, and up to nlam steps backward, in
-// one launch each (512^2, m = 12, 100 steps: 44.0 -> 26.6 ms; as sweeps each step
-// was 14 launches of about 11 us); the contractions of those backward steps
-// follow from the bases the launch leaves.
+// resident steps run a whole segment forward in one launch, and backward in groups:
+// a group's states, bases and scalars go to the slots of steps that are already
+// contracted, those of the next segment where it has a slot of its own (the whole
+// segment is one group), else the segment's own (the groups double in length: 1, 1,
+// 2, 4, .. steps), so nothing is stored beyond what the steps one by one need; the
+// contractions of a group follow from what its launch leaves.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -60,8 +62,6 @@ constexpr int kObserveBlocks = 1024;
 #define DL_ADJ_KEEP_GIB 32
 #endif
 constexpr size_t kKeepBasesBytes = size_t(DL_ADJ_KEEP_GIB) << 30;
-// Largest store of the bases of one resident backward launch.
-constexpr size_t kLamBasesBytes = size_t(8) << 30;
 
 struct AdjLayout {
     size_t sc = 0, alpha = 0, gamma = 0, obs = 0, fields = 0, cpart = 0, rec = 0, basis = 0, lam = 0,
@@ -80,13 +80,10 @@ struct AdjLayout {
     size_t kb_stride = 0, ks_stride = 0, ks_alpha = 0, ks_gamma = 0;
     size_t seg_slot = 0, kb_slot = 0, ks_slot = 0;  // bytes per slot
     int nfold = 1;  // contraction partial tables (one per backward step until the fold)
-    // grids that take resident steps: nlam backward steps run in one launch,
-    // which leaves their Krylov bases (lbasis), scalars (lscal) and states for
-    // the contractions after it (0: step by step, as sweeps); without kept
-    // bases the forward basis of a step is rebuilt by a launch of its own into
-    // the context's basis, its scalars in kscal, its end state in `spare`
-    int nlam = 0;
-    size_t lbasis = 0, lscal = 0, spare = 0;
+    // resident backward steps: scalars of the lambda basis while it is in `basis`
+    // (lscal); without kept bases the forward basis of a step is rebuilt by a
+    // launch of its own into the context's basis, its scalars in kscal
+    size_t lscal = 0;
 };
 
 AdjLayout adj_plan(const dl_params &p, int n_steps, int ckpt_every)
@@ -114,14 +111,10 @@ AdjLayout adj_plan(const dl_params &p, int n_steps, int ckpt_every)
     A.rec = off;
     off = align256(off + sizeof(double) * dl::kRecLen * (size_t)A.seglen);
     A.kb_stride = (size_t)(m - 1) * vec_stride(n, 16);
-    const bool resident = dl::resident_tiles(p.nx, p.ny, dl::kResidentWgs).rows > 0;
-    if (resident)
-        A.nlam = (int)std::max<size_t>(
-            1, std::min<size_t>((size_t)A.nfold, kLamBasesBytes / std::max<size_t>(A.kb_stride, 1)));
     A.basis = off;
     off += (size_t)(m - 1) * vec_stride(n, 16);
     A.lam = off;
-    off += (size_t)(std::max(A.nlam, 1) + 1) * vb;
+    off += 2 * vb;
     A.keep = A.kb_stride * (size_t)A.seglen <= kKeepBasesBytes;
     A.seg_slot = (size_t)(A.seglen + 1) * vb;
     A.ks_alpha = align256(sizeof(dl::Scalars));
@@ -144,19 +137,12 @@ AdjLayout adj_plan(const dl_params &p, int n_steps, int ckpt_every)
         A.kscal = off;
         off += (size_t)A.nslot * A.ks_slot;
     }
-    if (A.nlam > 0) {
-        off = align256(off);
-        A.lbasis = off;
-        off += (size_t)A.nlam * A.kb_stride;
-        off = align256(off);
-        A.lscal = off;
-        off += (size_t)A.nlam * A.ks_stride;
-        if (!A.keep) {
-            A.kscal = off;
-            off = align256(off + A.ks_stride);
-            A.spare = off;
-            off += vb;
-        }
+    off = align256(off);
+    A.lscal = off;
+    off += A.ks_stride;
+    if (!A.keep) {
+        A.kscal = off;
+        off += A.ks_stride;
     }
     A.total = off;
     return A;
@@ -335,7 +321,7 @@ static dl_status adjoint_run(dl_context *ctx, const void *psi0_v, double t0, dou
         const int len = seg_len(g);
         DL_HIP(ctx, hipMemcpyAsync(seg(g, 0), ckpt(g), n * 16, hipMemcpyDeviceToDevice, st));
         int first = 0;
-        while (first < len && A.nlam > 0 && ctx->resident.rows > 0) {
+        while (first < len && ctx->resident.rows > 0) {
             ResidentRun r;
             r.psi[0] = r.psi[1] = seg(g, first);
             r.state_stride = vb;
@@ -453,23 +439,35 @@ static dl_status adjoint_run(dl_context *ctx, const void *psi0_v, double t0, dou
                 pending = 0;
             }
         };
+        double2 *lnow = lam(cur);  // lambda at the end of step i
+        auto move_lam = [&](double2 *to) -> dl_status {
+            if (lnow != to) DL_HIP(ctx, hipMemcpyAsync(to, lnow, n * 16, hipMemcpyDeviceToDevice, st));
+            lnow = to;
+            return DL_OK;
+        };
         for (int i = len - 1; i >= 0;) {
             const size_t ns = (size_t)g * C + i;
             dl_status s = DL_OK;
-            // backward steps i, i - 1, .. in one launch; without kept bases one
-            // step, after the forward basis of step i
-            if (A.nlam > 0 && ctx->resident.rows > 0) {
-                const int nb = A.keep ? std::min(i + 1, A.nlam) : 1;
+            // backward steps i, i - 1, .. in one launch, as many as there are
+            // contracted steps in slots (segment gs, from step i0), which take their
+            // bases and scalars; their states take the places of states i0, i0 + 1,
+            // ...  Without such steps one step, into the buffers of the steps one
+            // by one
+            if (ctx->resident.rows > 0) {
+                const bool next = A.nslot > 1 && g + 1 < G;
+                const int gs = next ? g + 1 : g, i0 = next ? 0 : i + 1;
+                const int slots = A.keep ? std::min(next ? len : len - i0, dl::kChunk) : 0;
+                const int nb = std::max(1, std::min(i + 1, slots));
                 int done = 0;
                 ResidentRun r;
                 r.vstride = vstride;
                 r.stats = dstat;
+                r.state_stride = vb;
                 r.keep_alpha = A.ks_alpha;
                 r.keep_gamma = A.ks_gamma;
                 r.keep_step = A.ks_stride;
-                if (!A.keep) {
-                    r.psi[0] = seg(g, i);
-                    r.psi[1] = reinterpret_cast<double2 *>(aw + A.spare);
+                if (!A.keep) {  // the forward basis of step i (and state i + 1 again)
+                    r.psi[0] = r.psi[1] = seg(g, i);
                     r.basis = ep.basis;
                     r.fields = fields + 4 * ns;
                     r.keep = aw + A.kscal;
@@ -477,29 +475,31 @@ static dl_status adjoint_run(dl_context *ctx, const void *psi0_v, double t0, dou
                     if (s != DL_OK) return s;
                 }
                 if (A.keep || done == 1) {
-                    r.psi[0] = r.psi[1] = lam(0);
-                    r.state_stride = vb;
-                    r.basis = aw + A.lbasis;
+                    s = move_lam(slots > 0 ? seg(gs, i0) : lam(0));
+                    if (s != DL_OK) return s;
+                    cur = 0;
+                    r.psi[0] = r.psi[1] = lnow;
+                    r.basis = slots > 0 ? step_engine(gs, i0).basis : el.basis;
                     r.basis_step = A.kb_stride;
                     r.fields = fields + 4 * ns + 2;
                     r.field_stride = -4;
-                    r.keep = aw + A.lscal;
+                    r.keep = slots > 0 ? kept_scal(gs, i0) : aw + A.lscal;
                     s = run_resident(ctx, el, opb, r, 0, nb, &done);
                     if (s != DL_OK) return s;
-                    if (done == nb) {
-                        for (int j = 0; j < nb; ++j) {
-                            const char *ks = aw + A.lscal + (size_t)j * A.ks_stride;
-                            contract(i - j, lam(j), r.basis + (size_t)j * A.kb_stride,
-                                     reinterpret_cast<const dl::Scalars *>(ks),
-                                     reinterpret_cast<const double *>(ks + A.ks_alpha),
-                                     reinterpret_cast<const double *>(ks + A.ks_gamma), true);
-                        }
-                        DL_HIP(ctx, hipMemcpyAsync(lam(0), lam(nb), n * 16, hipMemcpyDeviceToDevice, st));
-                        i -= nb;
-                        continue;
+                    for (int j = 0; j < done; ++j) {
+                        const char *ks = r.keep + (size_t)j * A.ks_stride;
+                        contract(i - j, lnow, r.basis + (size_t)j * A.kb_stride,
+                                 reinterpret_cast<const dl::Scalars *>(ks),
+                                 reinterpret_cast<const double *>(ks + A.ks_alpha),
+                                 reinterpret_cast<const double *>(ks + A.ks_gamma), true);
+                        lnow = reinterpret_cast<double2 *>(reinterpret_cast<char *>(lnow) + vb);
                     }
+                    i -= done;
+                    if (done > 0) continue;
                 }
             }
+            s = move_lam(lam(cur));
+            if (s != DL_OK) return s;
             const Engine ei = step_engine(g, i);
             if (!A.keep) {
                 s = run_build(ctx, ei, opf, seg(g, i), fields + 4 * ns, partials, 1, true);
@@ -514,7 +514,12 @@ static dl_status adjoint_run(dl_context *ctx, const void *psi0_v, double t0, dou
             if (s != DL_OK) return s;
             contract(i, lam(cur), el.basis, el.sc, el.alpha, el.gamma, A.keep);
             cur = 1 - cur;
+            lnow = lam(cur);
             --i;
+        }
+        {
+            const dl_status s = move_lam(lam(cur));  // the segment's slot may be used again
+            if (s != DL_OK) return s;
         }
         DL_HIP(ctx, hipGetLastError());
         DL_HIP(ctx, hipMemcpyAsync(hrec.data(), rec, sizeof(double) * dl::kRecLen * len, hipMemcpyDeviceToHost, st));

@@ -84,6 +84,24 @@ def test_workspace_bytes_plan():
     assert binding.dirac_lanczos_workspace_bytes(p1, 4, 10) == 0
 
 
+@pytest.mark.parametrize("n,m,steps,every,keep", [(512, 12, 100, 50, True), (1024, 12, 200, 50, True),
+                                                  (512, 12, 400, 400, False), (64, 1, 5, 1, True)])
+def test_adjoint_workspace_bytes_plan(n, m, steps, every, keep):
+    """The checkpoints, one Krylov basis, two states of lambda, the states of a
+    segment (and its bases, for as many segments as fit in 32 GiB, where one does)
+    and 8 KiB x 1024 partials per step of a fold: nothing that grows with how the
+    backward steps are launched."""
+    cfg = packets.with_grid(packets.fourier_pulse_512(), n)
+    vb = 2 * n * n * 16
+    basis = (m - 1) * (vb + 8192)  # (vectors are padded by at most that)
+    nseg = -(-steps // every)
+    slots = max(1, min(nseg, (32 << 30) // ((m - 1) * vb * every + (every + 1) * vb))) if keep else 1
+    most = ((nseg - 1) * vb + basis + 2 * vb + slots * ((every + 1) * vb + (basis * every if keep else 0))
+            + min(64, every) * 1024 * 8192)
+    # records of a segment (under 16 KiB a step) and small arrays
+    assert binding.dirac_lanczos_adjoint_workspace_bytes(_params(cfg, m, 0), steps, every) <= most + every * 16384 + (2 << 20)
+
+
 @pytest.mark.parametrize("bad", [
     dict(nx=2), dict(ny=1), dict(x_max=-50.0), dict(bc_x=2), dict(c=0.0), dict(mass=-1.0),
     dict(pot_kind=3), dict(pot_kind=1, pot_a=0.0), dict(pot_kind=2, pot_z=0.0), dict(pulse_kind=5),

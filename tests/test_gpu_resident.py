@@ -162,6 +162,51 @@ def test_adjoint_without_kept_bases(torch_cuda):
     assert np.array_equal(res[0][1], res[1][1])
 
 
+@pytest.mark.parametrize("steps,ckpts", [(20, (1, 2, 3, 7, 19, 20)), (140, (140, 70, 133))])
+def test_adjoint_groups_of_backward_steps(torch_cuda, steps, ckpts):
+    """The backward steps of a segment run in groups that double in length, in the
+    slots of the steps before them (140: a group longer than a launch): the loss and
+    the gradient do not depend on the segments, bit for bit, and agree with those of
+    single steps as sweeps."""
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    prob = box(120, 100, 1, 0, pulse_kind=2, t_pulse=0.5, coef=np.array([10.0, -5.0, 3.0, 8.0]), **FIELDS)
+    psi0 = torch.from_numpy(packets.gaussian_packet(prob, 1.0, (1.0, -2.0))).cuda()
+    prop = Propagator(prob, 7, "fp64")
+    res = []
+    for ckpt in ckpts:
+        say(f"adjoint 120x100 {steps} steps, segments of {ckpt}")
+        res.append(prop.adjoint(psi0, 0.0, 1e-3, steps, ckpt, 15))
+    prop.set_wait(0.0)
+    loss, grad = prop.adjoint(psi0, 0.0, 1e-3, steps, ckpts[-1], 15)
+    prop.close()
+    for r in res[1:]:
+        assert r[0] == res[0][0]
+        assert np.array_equal(r[1], res[0][1])
+    # both ways round like the step phase |dt H| per step, 64 roundings of it allowed,
+    # on loss terms of up to |p| ~ 2 and |x| ~ 6 and their gradients
+    phase = 1e-3 * (C * C + 2 * C / 0.1 + 10 * C)
+    assert abs(loss - res[0][0]) <= 64 * steps * phase * EPS * 10.0
+    assert np.max(np.abs(grad - res[0][1])) <= 64 * steps * phase * EPS * max(np.max(np.abs(grad)), 10.0)
+
+
+def test_adjoint_with_one_slot(torch_cuda):
+    """Two segments whose bases fit in the kept store one at a time (512^2, m = 12,
+    200 steps: 20 GB each): the second is run again in the slot that the first leaves."""
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    cfg = packets.fourier_pulse_512()
+    psi0 = torch.from_numpy(packets.initial_state(cfg)).cuda()
+    prop = Propagator(cfg["problem"], cfg["m"], "fp64")
+    res = []
+    for ckpt in (200, 50):
+        say(f"adjoint 512x512 400 steps, segments of {ckpt}")
+        res.append(prop.adjoint(psi0, 0.0, cfg["dt"], 400, ckpt, 9))
+    prop.close()
+    assert res[0][0] == res[1][0]
+    assert np.array_equal(res[0][1], res[1][1])
+
+
 def test_contexts_on_one_workspace(torch_cuda, orc):
     """Two grids' contexts on the same workspace memory, used in turn: words that
     one leaves in the other's exchange buffers are never taken for its own."""
