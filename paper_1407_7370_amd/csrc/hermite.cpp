@@ -191,7 +191,13 @@ HermLayout herm_plan(const dl_hermite_params *p, int np, int k_max)
         off += sizeof(double) * 2 * (size_t)std::max(k_max, 1);
     }
     off = align256(off);
-    if (k_max <= dl::kHermRitzK) {
+    // The device's Ritz step takes as long for one problem as for a device full of
+    // them (chains of k_max rows); the host's grows with problems and k_max.  Up to
+    // k_max / 32 problems the host is as fast or faster.  ms a call, n = 16, five values
+    // in the window, host and device: 1 problem k = 400 1.55 and 2.66, k = 1000 4.4 and
+    // 6.0; 16 problems k = 400 2.5 and 2.8; 32 problems k = 400 3.5 and 2.8, k = 1000
+    // (one value) 7.9 and 6.0; 256 problems k = 400 17.1 and 3.7.
+    if (k_max <= dl::kHermRitzK && k_max <= 32 * (long)np) {
         L.ncheck = (k_max + kEigenCheckEvery - 1) / kEigenCheckEvery;
         L.ritz = off;
         off = align256(off + sizeof(double) * dl::kHermRitzLen * (size_t)L.ncheck * np);
@@ -310,59 +316,70 @@ dl_status dirac_lanczos_hermite_eigen(const dl_hermite_params *params, int32_t n
             hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
         return herm_fail(DL_ERR_DEVICE, "synchronisation failed");
-    // problems that the device's Ritz step did not take (long recurrences,
-    // windows with many values) are solved here from their T
+    // blocks that the device's Ritz step did not take (windows with many values,
+    // calls it is not for) are solved here from their T
     auto record = [&](int i, int c) { return ritz.data() + ((size_t)i * L.ncheck + c) * dl::kHermRitzLen; };
-    std::vector<char> here(n_problems, L.ncheck == 0);
-    bool nonfinite = false, any_here = L.ncheck == 0;
+    struct Block {
+        int i, k;  // problem, dimension
+        std::vector<double> ev, bd;
+    };
+    std::vector<Block> blocks;  // by problem, then dimension
+    bool nonfinite = false;
     for (int i = 0; i < n_problems; ++i) {
         if (runs[i].keff < 0) nonfinite = true;
-        n_found[i] = 0;
-        for (int c = 0; c < L.ncheck && !here[i] && runs[i].keff > 0; ++c) here[i] = record(i, c)[0] < 0.0;
-        any_here = any_here || here[i];
+        for (int c = 0; c * kEigenCheckEvery < runs[i].keff; ++c)
+            if (L.ncheck == 0 || record(i, c)[0] < 0.0)
+                blocks.push_back({i, std::min((c + 1) * kEigenCheckEvery, (int)runs[i].keff), {}, {}});
     }
-    if (any_here) {
+    if (!blocks.empty()) {
         ab.resize((size_t)2 * k_max * n_problems);
         if (hipMemcpyAsync(ab.data(), ws + L.ab0, sizeof(double) * ab.size(), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return herm_fail(DL_ERR_DEVICE, "synchronisation failed");
     }
-    // converged clusters accumulated over the leading blocks k = 64, 128, ...
-    // and k; problems are independent and spread over host threads
-    std::atomic<int> next{0};
-    const int nt = any_here ? std::max(1, std::min<int>(n_problems, host_threads())) : 1;
-    const int per_problem = std::max(1, host_threads() / nt);  // a few problems: checkpoints in parallel too
+    std::vector<int> order(blocks.size());  // the largest first
+    for (size_t j = 0; j < order.size(); ++j) order[j] = (int)j;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return blocks[x].k > blocks[y].k; });
+    std::atomic<size_t> next{0};
     auto worker = [&] {
-        for (int i; (i = next.fetch_add(1)) < n_problems;) {
-            const int k = runs[i].keff;
-            if (k <= 0) continue;
-            std::vector<std::pair<double, double>> found;
-            if (here[i]) {
-                const double *al = ab.data() + (size_t)2 * k_max * i, *be = al + k_max;
-                converged_union(al, be, k, e_lo[i], e_hi[i], tol, kEigenCheckEvery, per_problem, found);
-            } else {
-                for (int c = 0; c * kEigenCheckEvery < k; ++c) {
-                    const double *r = record(i, c);
-                    const int nw = (int)r[0];
-                    const std::vector<double> lam(r + 2, r + 2 + nw),
-                        zl(r + 2 + dl::kHermRitzMax, r + 2 + dl::kHermRitzMax + nw);
-                    double ev[dl::kHermRitzMax], bd[dl::kHermRitzMax];
-                    const int nf = ritz_select(lam, zl, r[1], e_lo[i], e_hi[i], tol, dl::kHermRitzMax, ev, bd, nullptr);
-                    merge_converged(found, ev, bd, nf, tol);
-                }
-            }
-            const int nf = std::min((int)found.size(), n_wanted);
-            for (int r = 0; r < nf; ++r) {
-                evals[(size_t)i * n_wanted + r] = found[r].first;
-                bounds[(size_t)i * n_wanted + r] = found[r].second;
-            }
-            n_found[i] = nf;
+        for (size_t j; (j = next.fetch_add(1)) < order.size();) {
+            Block &b = blocks[order[j]];
+            const double *al = ab.data() + (size_t)2 * k_max * b.i;
+            std::vector<double> ev(b.k), bd(b.k);
+            const int nf = ritz_chain(al, al + k_max, b.k, e_lo[b.i], e_hi[b.i], tol, b.k, ev.data(), bd.data(), nullptr,
+                                      nullptr);
+            b.ev.assign(ev.begin(), ev.begin() + nf);
+            b.bd.assign(bd.begin(), bd.begin() + nf);
         }
     };
     std::vector<std::thread> pool;
-    for (int t = 1; t < nt; ++t) pool.emplace_back(worker);
+    for (int t = 1; t < std::min<int>(host_threads(), (int)blocks.size()); ++t) pool.emplace_back(worker);
     worker();
     for (auto &th : pool) th.join();
+    // converged clusters accumulated over the leading blocks k = 64, 128, ... and k
+    auto block = blocks.cbegin();
+    for (int i = 0; i < n_problems; ++i) {
+        std::vector<std::pair<double, double>> found;
+        for (int c = 0; c * kEigenCheckEvery < runs[i].keff; ++c) {
+            if (L.ncheck == 0 || record(i, c)[0] < 0.0) {
+                merge_converged(found, block->ev.data(), block->bd.data(), (int)block->ev.size(), tol);
+                ++block;
+                continue;
+            }
+            const double *r = record(i, c);
+            const int nw = (int)r[0];
+            const std::vector<double> lam(r + 2, r + 2 + nw), zl(r + 2 + dl::kHermRitzMax, r + 2 + dl::kHermRitzMax + nw);
+            double ev[dl::kHermRitzMax], bd[dl::kHermRitzMax];
+            const int nf = ritz_select(lam, zl, r[1], e_lo[i], e_hi[i], tol, dl::kHermRitzMax, ev, bd, nullptr);
+            merge_converged(found, ev, bd, nf, tol);
+        }
+        const int nf = std::min((int)found.size(), n_wanted);
+        for (int r = 0; r < nf; ++r) {
+            evals[(size_t)i * n_wanted + r] = found[r].first;
+            bounds[(size_t)i * n_wanted + r] = found[r].second;
+        }
+        n_found[i] = nf;
+    }
     if (nonfinite) return herm_fail(DL_ERR_NONFINITE, "non-finite Lanczos reduction in a Hermite problem");
     return DL_OK;
 }

@@ -78,3 +78,28 @@ def test_device_and_host_ritz_agree(torch_cuda):
     assert len(none) == 0
     one, b1 = eigen(torch_cuda, hp, start, 1, 0.0, 2.0 * MC2, 1e9)
     assert len(one) == 1 and b1[0] > 0
+
+
+@pytest.mark.parametrize("n,k,problems", [(32, 1024, 40), (16, 300, 12), (64, 700, 22)])
+def test_many_problems_agree_with_one_at_a_time(torch_cuda, n, k, problems):
+    """The Ritz step runs on the device for at least k / 32 problems, on the host for
+    fewer, and a block of a device call whose window holds more values than the
+    device keeps per block goes to the host by itself (the later blocks of the wide
+    windows here)."""
+    from paper_1407_7370_amd import binding
+    torch = torch_cuda
+    tol = 1e-5
+    zs = np.linspace(2.0, 40.0, problems)
+    hps = [packets.softcore_hermite(float(z), n=n) for z in zs]
+    starts = [torch.from_numpy(packets.hermite_packet(h, 1 / z, (0.4 / z, 0.25 / z))).cuda() for h, z in zip(hps, zs)]
+    # narrow, wide and empty windows in turn
+    lo = [MC2 - 0.7 * z * z for z in zs]
+    hi = [MC2 + (-0.14, 3.0, -0.69)[i % 3] * z * z for i, z in enumerate(zs)]
+    say(f"hermite {problems} problems n={n} k={k}: together")
+    many = binding.hermite_eigen(hps, starts, k, lo, hi, tol, 64)
+    say("one at a time")
+    found = 0
+    for i in range(problems):
+        (ev, bd), = binding.hermite_eigen(hps[i:i + 1], starts[i:i + 1], k, lo[i:i + 1], hi[i:i + 1], tol, 64)
+        found += hz.match_converged(*many[i], ev, bd, tol)
+    assert found >= problems // 3
