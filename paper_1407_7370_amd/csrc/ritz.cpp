@@ -11,6 +11,7 @@
 #include <cstdint>
 #include <system_error>
 #include <thread>
+#include <type_traits>
 
 namespace dlh {
 
@@ -18,12 +19,63 @@ void tridiag_full(std::vector<double> d, std::vector<double> e, std::vector<doub
                   std::vector<double> &v)
 {
     const int k = (int)d.size();
-    // the rotations of the sweeps, applied to the eigenvectors afterwards
+    // The rotations of the sweeps are collected and applied to v a batch at a time
+    // (24 MiB; all of them for k up to about 900).  Every row of v takes the same
+    // rotations in the same order, so blocks of rows are independent: until the end
+    // each is held as contiguous columns (a rotation runs along two of them at full
+    // vector width), large problems on several threads.  k = 512: 0.95 s rotating the
+    // rows of v in place, 0.16 s by columns, 0.05 s by blocks on eight threads.
     struct Rot {
         int q;
         double c, s;
     };
+    constexpr int kRows = 32;
+    constexpr size_t kBatch = size_t(1) << 20;
+    const int blocks = (k + kRows - 1) / kRows;
+    const int nt = std::min(blocks, k >= 128 ? host_threads() : 1);
     std::vector<Rot> rot;
+    v.assign((size_t)k * k, 0.0);
+    for (int r = 0; r < k; ++r) {  // the unit matrix: row r in column r of its block
+        const int r0 = r / kRows * kRows, n = std::min(kRows, k - r0);
+        v[(size_t)r0 * k + (size_t)r * n + (r - r0)] = 1.0;
+    }
+    // f(block, thread) for every block
+    auto for_blocks = [&](auto &&f) {
+        std::atomic<int> next{0};
+        auto worker = [&](int t) {
+            for (int b; (b = next.fetch_add(1)) < blocks;) f(b, t);
+        };
+        std::vector<std::thread> pool;
+        pool.reserve(nt);
+        try {
+            for (int t = 1; t < nt; ++t) pool.emplace_back(worker, t);
+        } catch (const std::system_error &) {  // no more threads: the ones there do the work
+        }
+        worker(0);
+        for (auto &th : pool) th.join();
+    };
+    auto rotate = [&rot](double *col, auto n) {
+        for (const Rot &r : rot) {
+            double *__restrict__ zq = col + (size_t)r.q * n, *__restrict__ zq1 = zq + n;
+            const double c = r.c, s = r.s;
+            for (int row = 0; row < n; ++row) {
+                const double a0 = zq[row], a1 = zq1[row];
+                zq[row] = c * a0 - s * a1;
+                zq1[row] = s * a0 + c * a1;
+            }
+        }
+    };
+    auto apply = [&] {
+        for_blocks([&](int b, int) {
+            double *col = v.data() + (size_t)b * kRows * k;
+            const int n = std::min(kRows, k - b * kRows);
+            if (n == kRows)
+                rotate(col, std::integral_constant<int, kRows>{});
+            else
+                rotate(col, n);
+        });
+        rot.clear();
+    };
     e.resize(k, 0.0);
     const double eps = 2.220446049250313e-16;
     int h = k - 1, iter = 0;
@@ -62,44 +114,19 @@ void tridiag_full(std::vector<double> d, std::vector<double> e, std::vector<doub
             }
             rot.push_back(Rot{q, c, s});
         }
+        if (rot.size() >= kBatch) apply();
     }
     lam = d;
-    v.resize((size_t)k * k);
-    // Every row of v takes the same rotations in the same order, so blocks of
-    // rows are independent: each is held as contiguous columns (a rotation runs
-    // along two of them at full vector width), large problems on several threads.
-    // k = 512: 0.95 s rotating the rows of v in place, 0.16 s by columns, 0.05 s
-    // by blocks on eight threads.
-    constexpr int kRows = 32;
-    auto block = [&](int r0) {
-        const int n = std::min(kRows, k - r0);
-        std::vector<double> col((size_t)k * kRows, 0.0);
-        for (int i = 0; i < n; ++i) col[(size_t)(r0 + i) * kRows + i] = 1.0;
-        for (const Rot &r : rot) {
-            double *__restrict__ zq = col.data() + (size_t)r.q * kRows, *__restrict__ zq1 = zq + kRows;
-            const double c = r.c, s = r.s;
-            for (int row = 0; row < kRows; ++row) {
-                const double a0 = zq[row], a1 = zq1[row];
-                zq[row] = c * a0 - s * a1;
-                zq1[row] = s * a0 + c * a1;
-            }
-        }
+    apply();
+    // the blocks row by row
+    std::vector<double> tmp((size_t)nt * kRows * k);
+    for_blocks([&](int b, int t) {
+        double *col = v.data() + (size_t)b * kRows * k, *rows = tmp.data() + (size_t)t * kRows * k;
+        const int n = std::min(kRows, k - b * kRows);
         for (int i = 0; i < n; ++i)
-            for (int j = 0; j < k; ++j) v[(size_t)(r0 + i) * k + j] = col[(size_t)j * kRows + i];
-    };
-    const int blocks = (k + kRows - 1) / kRows;
-    const int nt = std::min(blocks, k >= 128 ? host_threads() : 1);
-    std::atomic<int> next{0};
-    auto worker = [&] {
-        for (int b; (b = next.fetch_add(1)) < blocks;) block(b * kRows);
-    };
-    std::vector<std::thread> pool;
-    try {
-        for (int t = 1; t < nt; ++t) pool.emplace_back(worker);
-    } catch (const std::system_error &) {  // no more threads: the ones there do the work
-    }
-    worker();
-    for (auto &th : pool) th.join();
+            for (int j = 0; j < k; ++j) rows[(size_t)i * k + j] = col[(size_t)j * n + i];
+        std::copy(rows, rows + (size_t)n * k, col);
+    });
 }
 
 namespace {

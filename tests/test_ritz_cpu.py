@@ -132,3 +132,56 @@ def test_rejections():
             binding.ritz(al, be, args["e_lo"], args["e_hi"], args["tol"], args["check_every"], args["n_wanted"])
     with pytest.raises(binding.DlError):
         binding.ritz(al[:0], be[:0], 0.0, 1.0, 1e-6)
+
+
+def test_full_decomposition_memory(tmp_path):
+    """All eigenvectors of T (tridiag_full, behind eigen_vectors and the adjoint) at
+    k = 2000: an orthonormal decomposition to rounding, within four times the memory
+    of the eigenvectors (the rotations of the sweeps, 24 bytes each and about k^2 in
+    number, are not all held)."""
+    import os
+    import subprocess
+    src = r"""
+#include "ritz.h"
+#include <cmath>
+#include <cstdio>
+#include <sys/resource.h>
+static long rss() { struct rusage r; getrusage(RUSAGE_SELF, &r); return r.ru_maxrss; }
+int main() {
+    const int k = 2000;
+    std::vector<double> d(k), e(k), lam, v;
+    unsigned long long s = 88172645463325252ull;
+    auto rnd = [&] { s ^= s << 13; s ^= s >> 7; s ^= s << 17; return (double)(s >> 11) / 9007199254740992.0; };
+    for (double &x : d) x = 2.0 * rnd() - 1.0;
+    for (double &x : e) x = rnd() + 0.1;
+    const long before = rss();
+    dlh::tridiag_full(d, e, lam, v);
+    const long used = rss() - before;
+    double res = 0.0, orth = 0.0;
+    for (int l = 0; l < k; l += 37) {
+        double r2 = 0.0, n2 = 0.0;
+        for (int i = 0; i < k; ++i) {
+            const double *row = &v[(size_t)i * k + l];
+            double t = (d[i] - lam[l]) * *row;
+            if (i > 0) t += e[i - 1] * row[-k];
+            if (i + 1 < k) t += e[i] * row[k];
+            r2 += t * t;
+            n2 += *row * *row;
+        }
+        res = std::fmax(res, std::sqrt(r2));
+        orth = std::fmax(orth, std::fabs(n2 - 1.0));
+    }
+    std::printf("%ld %.3e %.3e\n", used, res, orth);
+}
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    cpp = tmp_path / "full.cpp"
+    cpp.write_text(src)
+    exe = str(tmp_path / "full")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-pthread", f"-I{root}/include", f"-I{root}/paper_1407_7370_amd/csrc", str(cpp),
+                    f"{root}/paper_1407_7370_amd/csrc/ritz.cpp", "-o", exe], check=True)
+    used, res, orth = subprocess.run([exe], capture_output=True, text=True, check=True).stdout.split()
+    assert int(used) * 1024 <= 4 * 2000 * 2000 * 8
+    # k^2 rotations, each rounded to a few eps, errors adding up like a random walk; norm of T below 4
+    assert float(res) <= 4 * 8 * 2000 * 2.0 ** -52
+    assert float(orth) <= 8 * 2000 * 2.0 ** -52
