@@ -285,3 +285,30 @@ def test_orthonormal_at_chunk_edges(torch_cuda, Prop, nx, ny, bc, k):
     for th, y in zip(ev, M):
         # a cluster's mean is within tol of each member, whose bound is at most tol
         assert np.linalg.norm(H @ y - th * y) <= 2.0 * k * 1e-3 * norm
+
+
+# the whole space: all 2 nx ny values, at dimensions about the chunks of 16 and 256
+@pytest.mark.parametrize("nx,ny", [(3, 3), (4, 4), (3, 6), (9, 7), (8, 16), (3, 43), (16, 16)])
+def test_whole_space_decomposition(torch_cuda, Prop, nx, ny):
+    """k = dim: every eigenvalue of the dense H once (a basis that had lost its
+    orthogonality would give copies), with an orthonormal set of vectors whose
+    residuals are at rounding."""
+    torch = torch_cuda
+    prob = prob_of(nx, ny)
+    k = 2 * nx * ny
+    H = hz.dense_h(prob)
+    w = np.linalg.eigvalsh(H.toarray())
+    norm = np.abs(w).max()
+    # k iterations, each rounding H q and its projections to a few eps of ||H||
+    tol = 64 * k * 2.0 ** -52
+    assert np.diff(w).min() > 1e-6 + 2 * tol * norm  # (no value may merge with the next)
+    say(f"eigen reorth whole space {nx}x{ny} k={k}")
+    prop = Prop(prob, 1, "fp64", k_eigen=k, reorth=True)
+    ev, bd, Y = prop.eigen_vectors(torch.from_numpy(packets.random_spinor(prob, 7)).cuda(), k, -1e9, 1e9, 1e-6, n_wanted=k)
+    prop.close()
+    assert len(ev) == k
+    assert np.max(np.abs(ev - w)) <= tol * norm
+    M = Y.cpu().numpy().reshape(k, -1)
+    assert np.max(np.abs(M.conj() @ M.T - np.eye(k))) <= tol
+    for th, b, y in zip(ev, bd, M):
+        assert np.linalg.norm(H @ y - th * y) <= b + tol * norm
