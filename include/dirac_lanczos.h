@@ -488,8 +488,9 @@ const char *dirac_lanczos_hermite_last_error(void);
  *   64 steps instead of sweeps (except with an adaptive dimension, in the
  *   memory-saving variant and under stream capture), which this does not change.
  * dirac_lanczos_batch_set_launch: rows per chunk of the batched sweeps
- *   (>= 4; 0: the default choice, whose chunks spread most evenly over the
- *   resident workgroups).  *rows_out (HOST, may be NULL) receives it.
+ *   (>= 4; 0: the default choice: in mixed precision the rows whose chunks
+ *   spread most evenly over the resident workgroups, in FP64 the smallest power
+ *   of two giving at most eight chunks' entries a workgroup).  *rows_out (HOST, may be NULL) receives it.
  * The autotuner of the Python package times candidates and caches the best.
  */
 dl_status dirac_lanczos_set_launch(dl_context *ctx, int32_t sweep_waves_per_cu, int32_t *waves_out);

@@ -5,8 +5,7 @@
 // exponentials, the recombination) whatever the number of packets.
 //
 // Launch shape.  The sweeps of all packets use one common number R of rows per
-// chunk: the one whose entries, spread over the resident workgroups, finish first
-// (default_rows).  A packet's tasks (strip, chunk) are padded to a
+// chunk (default_rows).  A packet's tasks (strip, chunk) are padded to a
 // multiple of four so that a block entry's waves belong to one packet; the
 // entries of a packet form a contiguous segment (partials slots).  The
 // recombination gives every packet a number of workgroups proportional to its
@@ -188,19 +187,21 @@ long longest_list(std::vector<long> &cost, int G)
     return *std::max_element(heap.begin(), heap.end());
 }
 
-// Rows per chunk of the sweeps: from 16 in steps of four or a sixteenth, the one
-// whose longest list of entries is shortest.  Short chunks spend their rows in the
-// march's start, long ones do not spread evenly over the workgroups (more than
+// Rows per chunk of the sweeps.  Complex64: from 16 in steps of four or a sixteenth,
+// the one whose longest list of entries is shortest.  Short chunks spend their rows in
+// the march's start, long ones do not spread evenly over the workgroups (more than
 // eight entries each always do, so those sizes are passed over).  Beyond kLongRows
 // rows one round of entries is all there is, and its gain on paper is not there:
 // 128 packets of 128^2..512^2, 144 rows against 68, complex64 12.80 and 12.73 ms,
 // complex128 21.81 and 21.44.  Below 16 rows the start of the march weighs more than
 // entries on idle workgroups give (8 packets of 150^2..400^2, 8 rows against 16: 1.37
-// and 1.29 ms).  This choice against the smallest power of two with at most eight
-// entries a workgroup, per call of four steps: 128 packets complex64 12.75 against
-// 13.58 ms, 100 of 90^2..250^2 complex64 4.76 and 5.15, 40 of 150^2..400^2 3.53 and 3.96
-// (complex128 5.08 and 5.23).
-int default_rows(const std::vector<dl_params> &params, int G)
+// and 1.29 ms).  Complex128 sweeps are bound by memory whatever their balance, and take
+// the smallest power of two with at most eight entries a workgroup.
+// Shortest list against that power of two, ms a call of four steps, m = 12, packets of
+// {128, 192, 256, 384, 512}^2: complex64 512 of them 50.0 and 49.7, 256 26.6 and 26.6,
+// 128 11.9 and 14.5, 64 6.35 and 7.4, 32 2.96 and 3.05; complex128 77.9 and 78.2, 40.9
+// and 40.6, 20.0 and 20.4, 10.8 and 10.55, 4.23 and 4.08.
+int default_rows(const std::vector<dl_params> &params, int G, bool mixed)
 {
     int max_ny = 0;
     for (const dl_params &p : params) max_ny = std::max(max_ny, p.ny);
@@ -208,10 +209,11 @@ int default_rows(const std::vector<dl_params> &params, int G)
     long best_len = 0;
     std::vector<long> cost;
     constexpr int kLongRows = 96;
-    for (int R = 16; best == 0 || R <= kLongRows; R += std::max(4, R / 64 * 4)) {
+    for (int R = 16; best == 0 || R <= kLongRows; R += mixed ? std::max(4, R / 64 * 4) : R) {
         size_t entries = 0;
         for (const dl_params &p : params) entries += ceil_div((size_t)strips(p.nx, 2) * ceil_div(p.ny, R), dl::kWaves);
         if (entries > (size_t)8 * G && R < max_ny) continue;  // (when even whole strips are more, those)
+        if (!mixed) return R;
         cost.clear();
         for (const dl_params &p : params) {
             const int ns = strips(p.nx, 2), nch = (int)ceil_div(p.ny, R), tail = p.ny - (nch - 1) * R;
@@ -235,7 +237,7 @@ dl_status build_tables(dl_batch *b, int rows_per_chunk)
 {
     const int n = b->n;
     const std::vector<dl_params> &params = b->p;
-    const int R = rows_per_chunk > 0 ? rows_per_chunk : default_rows(params, dl::kBatchWgsPerCu * b->cus);
+    const int R = rows_per_chunk > 0 ? rows_per_chunk : default_rows(params, dl::kBatchWgsPerCu * b->cus, params[0].precision == DL_PREC_MIXED);
     if (R < 4) return b->fail(DL_ERR_INVALID, "rows per chunk must be >= 4");
     b->rows = R;
     std::vector<dl::BatchBlock> blk[dl::kGridKinds];

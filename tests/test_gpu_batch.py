@@ -223,3 +223,20 @@ def test_launch_shapes_agree_to_rounding(torch_cuda, tmp_path):
                             candidates=(8, 0), cache=cache)
     assert e["best"] in (8, 0)
     assert autotune.lookup(autotune.key_batch(probs, 10, "fp64", autotune.device_arch()), cache) == e["best"]
+
+
+@pytest.mark.parametrize("n,size", [(3, 70), (64, 256), (300, 250)])
+def test_default_rows_fp64(torch_cuda, n, size):
+    """The default rows per chunk of complex128 batches: the smallest power of two
+    from 16 with at most eight block entries (four strips of 60 columns by R rows) a
+    resident workgroup (two per compute unit)."""
+    from paper_1407_7370_amd.binding import BatchPropagator
+    say(f"default rows of {n} packets of {size}x{size} fp64")
+    bp = BatchPropagator([prob(size, size)] * n, 4, "fp64")
+    rows = bp.set_launch(0)
+    bp.close()
+    most = 8 * 2 * torch_cuda.cuda.get_device_properties(0).multi_processor_count
+    R = 16
+    while n * -(-(-(-size // 60) * -(-size // R)) // 4) > most and R < size:
+        R *= 2
+    assert rows == R
