@@ -85,10 +85,11 @@ def _time_steps(step, steps: int) -> float:
 
 def tune_single(problem: dict, psi0, m: int, precision: str, dt: float, steps: int = 4,
                 candidates=SINGLE_CANDIDATES, cache: str = DEFAULT_CACHE) -> dict:
-    """Time each sweep cap on `steps` steps of the problem; store and return the result."""
+    """Time each sweep cap on `steps` steps of the problem as sweeps; store and return the result."""
     import torch
     from .binding import Propagator
     prop = Propagator(problem, m, precision)
+    prop.set_wait(0.0)  # the cap is for sweeps: no resident launches
     times = {}
     for c in candidates:
         used = prop.set_launch(c)
