@@ -452,7 +452,7 @@ void launch_lanczos_local(const Op &op, const double2 *q, const double2 *qm, dou
 // ||z|| and the breakdown test, unless a second pass has to follow (Scalars::again),
 // which the call with `second` does where the flag asks for it.
 void launch_orth(const char *q, size_t vstride, int nvec, double2 *z, size_t nelem, double *pproj, double *h,
-                 const double *alpha, double *beta, Scalars *sc, double *partials, int nblocks, bool second,
+                 double *alpha, double *beta, Scalars *sc, double *partials, int nblocks, bool second,
                  hipStream_t st);
 // beta_0 = ||psi||, q_1 = psi / beta_0 (kstop = 0 when psi = 0).
 void launch_first_q(const double2 *psi, size_t nelem, double2 *q1, Scalars *sc, double *beta, double *partials,

@@ -218,12 +218,13 @@ __device__ __forceinline__ void norm_update(double zz, int i, const double *alph
     if (b <= 1e-13 * scale) sc->kstop = i;
 }
 
-// z -= sum_j h_j q_j and ||z||^2; the last workgroup decides whether a second pass
-// follows, else updates the scalars of iteration i = nvec.  The loop over element tiles has a workgroup-uniform
+// z -= sum_j h_j q_j and ||z||^2; the last workgroup adds Re h_i (what rounding left
+// along q_i) to alpha_i, decides whether a second pass follows, and else updates the
+// scalars of iteration i = nvec.  The loop over element tiles has a workgroup-uniform
 // trip count (the LDS staging of h needs every thread at the barriers).
 __global__ __launch_bounds__(kBlock) void k_sub_q(const char *__restrict__ q, size_t vstride, int nvec,
                                                   const double *__restrict__ h, double2 *__restrict__ z,
-                                                  size_t nelem, const double *alpha, double *beta, Scalars *sc,
+                                                  size_t nelem, double *alpha, double *beta, Scalars *sc,
                                                   double *partials, int second)
 {
     if (second && !sc->again) return;
@@ -277,6 +278,7 @@ __global__ __launch_bounds__(kBlock) void k_sub_q(const char *__restrict__ q, si
         hh = b[0];
     }
     if (threadIdx.x != 0) return;
+    if (sc->kstop >= nvec) alpha[nvec] += h[2 * (nvec - 1)];
     sc->again = !second && hh > kAgain * kAgain * tot[0];
     if (!sc->again) norm_update(tot[0], nvec, alpha, beta, sc);
 }
@@ -564,7 +566,7 @@ void launch_lanczos_local(const Op &op, const double2 *q, const double2 *qm, dou
 }
 
 void launch_orth(const char *q, size_t vstride, int nvec, double2 *z, size_t nelem, double *pproj, double *h,
-                 const double *alpha, double *beta, Scalars *sc, double *partials, int nblocks, bool second,
+                 double *alpha, double *beta, Scalars *sc, double *partials, int nblocks, bool second,
                  hipStream_t st)
 {
     const int nchunk = (nvec + kDotVecs - 1) / kDotVecs;
