@@ -424,7 +424,10 @@ dl_status take_async_failure(dl_context *ctx)
     if (hs.status == 0) return DL_OK;
     dl::launch_reset(ctx->sc(), ctx->stream);
     DL_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    return ctx->status_fail(hs.status, "in an asynchronous call after " + std::to_string(hs.steps_done) + " of its steps");
+    const dl_status s =
+        ctx->status_fail(hs.status, "in an asynchronous call after " + std::to_string(hs.steps_done) + " of its steps");
+    ctx->timed_out = false;  // (not of the call that reports it)
+    return s;
 }
 
 }  // namespace dlh

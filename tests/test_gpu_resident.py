@@ -360,3 +360,27 @@ def test_timing_across_the_end_of_resident_steps(torch_cuda):
     assert sum(ms for _, ms in both.values()) <= 1.05 * wall
     assert sum(ms for _, ms in both.values()) >= 0.5 * sum(resident.values())
     assert sum(n for n, _ in both.values()) == 51 * (9 + 2)
+
+
+@pytest.mark.parametrize("call", ["step", "eigen", "adjoint"])
+def test_synchronous_calls_report_an_asynchronous_time_out(torch_cuda, call):
+    """The next synchronous call reports a time-out of an asynchronous one and does
+    nothing else; the call after it runs."""
+    from paper_1407_7370_amd import binding
+    from paper_1407_7370_amd.binding import Propagator
+    torch = torch_cuda
+    prob = box(400, 390, 1, 0, pulse_kind=2, t_pulse=0.05, coef=np.array([10.0, -5.0, 3.0, 8.0]), **FIELDS)
+    psi0 = torch.from_numpy(packets.gaussian_packet(prob, 1.0, (1.0, -2.0))).cuda()
+    prop = Propagator(prob, 6, "fp64", k_eigen=70)
+    run = {"step": lambda: prop.step(psi0.clone(), 0.0, 1e-4, 2), "eigen": lambda: prop.eigen(psi0, 70, -1e9, 1e9, 4e9),
+           "adjoint": lambda: prop.adjoint(psi0, 0.0, 1e-4, 3, 2, 9)}[call]
+    say(f"time-out of an asynchronous call reported by {call}")
+    prop.set_wait(1e-8)
+    x = psi0.clone()
+    prop.step_async(x, 0.0, 1e-4, 3)
+    with pytest.raises(binding.DlError) as ei:
+        run()
+    assert ei.value.status == binding.DL_ERR_DEVICE and "asynchronous" in str(ei.value)
+    assert torch.equal(x, psi0)
+    run()
+    prop.close()
