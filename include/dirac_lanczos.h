@@ -282,6 +282,12 @@ dl_status dirac_lanczos_step_adaptive(dl_context *ctx, void *psi, double t0, dou
  * within its earlier bound of an eigenvalue of H (Paige); values closer than
  * tol are one eigenvalue and keep their smallest bound; the call stops at
  * the first checkpoint with n_wanted values and reports the lowest n_wanted.
+ * Blocks with up to 64 values in the window (k <= 4096, finite e_lo, e_hi) are
+ * solved on the device, the others on the host as in dirac_lanczos_ritz.  The
+ * device takes each value's own eigenvector of T; values equal to rounding (a
+ * value and its copies) can get the same one, where the host keeps theirs
+ * orthogonal, so a cluster's bound may differ between the two.  Every such
+ * vector bounds its value's distance from an eigenvalue of H, so both hold.
  * reorth != 0: full
  * reorthogonalisation (Sec. 2): the recurrence's terms alpha_i q_i and
  * beta_{i-1} q_{i-1} are subtracted, then classical Gram-Schmidt runs against all
@@ -463,7 +469,8 @@ dl_status dirac_lanczos_hermite_apply(const dl_hermite_params *params, const voi
  * iterations in one launch; then, per problem, the converged Ritz clusters
  * of the leading blocks T_k, k = 64, 128, ... and k_max, in [e_lo[i],
  * e_hi[i]] with bound <= tol, accumulated as in dirac_lanczos_eigen with
- * reorth = 0.  evals/bounds: HOST arrays of n_problems * n_wanted (problem i
+ * reorth = 0 (on the device for at least k_max / 32 problems with k_max <= 2048,
+ * blocks with more than 16 values in the window and other calls on the host).  evals/bounds: HOST arrays of n_problems * n_wanted (problem i
  * at offset i * n_wanted, ascending), n_found: HOST array of n_problems.  A
  * start vector of norm 0 reports nothing.  Errors: DL_ERR_INVALID,
  * DL_ERR_WORKSPACE, DL_ERR_NONFINITE (a reduction of some problem became

@@ -33,6 +33,14 @@ __device__ __forceinline__ double lanes_sum(double v)
     return v;
 }
 
+// 1 / q to within an ulp or two (|q| between about 1e-300 and 1e300).
+__device__ __forceinline__ double recip(double q)
+{
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(r, fma(-q, r, 1.0), r);
+    return fma(r, fma(-q, r, 1.0), r);
+}
+
 template <int NV>
 __device__ __forceinline__ void wave_sum(double (&v)[NV])
 {

@@ -1,6 +1,6 @@
 // gfx950 kernels of the eigenvalue mode with full reorthogonalisation
 // (Sec. 2: the Lanczos vectors are kept and every new vector is
-// orthogonalised against all of them, twice) and of the Ritz vectors
+// orthogonalised against all of them, twice where needed) and of the Ritz vectors
 // (Sec. 2 eq. eigenvec_approx).
 //
 // Iteration i: z = H q_i - alpha_i q_i - beta_{i-1} q_{i-1} (k_eig_apply,
@@ -436,11 +436,6 @@ __global__ __launch_bounds__(kBlock) void k_ritz_window(const double *__restrict
     const double theta = 0.5 * (a + b);
     // pivots: negligible ones taken as negative
     auto keep = [](double q) { return fabs(q) < 1e-280 ? -1e-280 : q; };
-    auto recip = [](double q) {
-        double r = __builtin_amdgcn_rcp(q);
-        r = fma(r, fma(-q, r, 1.0), r);
-        return fma(r, fma(-q, r, 1.0), r);
-    };
     if (w == 0) {
         double q = 1.0, e2 = 0.0;
 #pragma unroll 8

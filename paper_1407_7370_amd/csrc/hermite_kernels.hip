@@ -362,14 +362,6 @@ __global__ __launch_bounds__(kHermBlock) void k_herm_lanczos(const HermOp *ops, 
     if (threadIdx.x == 0) run.keff = keff;
 }
 
-// 1 / q to within an ulp or two (|q| between about 1e-300 and 1e300).
-__device__ __forceinline__ double recip(double q)
-{
-    double r = __builtin_amdgcn_rcp(q);
-    r = fma(r, fma(-q, r, 1.0), r);
-    return fma(r, fma(-q, r, 1.0), r);
-}
-
 // Ritz values of one leading block (blockIdx.y: checkpoint, the largest first) of
 // one problem by one wave: T in LDS, Sturm counts of 64 shifts at a time (the
 // signs of the pivots of the LDL^T factorisation of T - x, a negligible pivot

@@ -817,7 +817,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
             const __amdgpu_buffer_rsrc_t o1 = row_rsrc(reinterpret_cast<const char *>(out) + plane, plane);
             // kPart rows at a time, two vectors' loads in flight (terms in the
             // order j = 2..k)
-                        constexpr int kPart = K <= 4 ? K : (K + 1) / 2;
+            constexpr int kPart = K <= 4 ? K : (K + 1) / 2;
 #pragma unroll
             for (int kb = 0; kb < K; kb += kPart) {
                 uint32_t site[kPart], boff[kPart];
@@ -838,7 +838,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
                 auto load = [&](int j, auto pol, Raw<TO>(&v)[kPart]) {
                     const __amdgpu_buffer_rsrc_t ub = row_rsrc(basis + (size_t)(j - 2) * a.vstride, vec_bytes);
 #pragma unroll
-                    for (int q = 0; q < kPart; ++q) 
+                    for (int q = 0; q < kPart; ++q)
                         v[q] = ld_site_at<TO, decltype(pol)::value>(ub, boff[q], bsecond);
                 };
                 auto add = [&](int j, const Raw<TO>(&v)[kPart]) {
