@@ -340,7 +340,17 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
     unsigned long long *const red = a.red, *const halo = a.halo;
     const size_t halo_buf = (size_t)NW * NS * nwg;
     uint32_t epoch = a.epoch;
-    const unsigned long long started = wall_clock64();
+    // whether this workgroup's waits are over.  The end is read from LDS where few
+    // rows a thread leave the registers to the iterations (64^2 959 -> 974 us a call of 20
+    // steps with it in registers), and kept in registers else (1024^2 2264 us a call of
+    // five steps, from LDS 2294)
+    const unsigned long long started = wall_clock64(), deadline = started + a.wait_ticks;
+    auto late = [&] {
+        if constexpr (kTwo)
+            return wall_clock64() > sh.deadline;
+        else
+            return wall_clock64() > deadline;
+    };
 
     const bool direct = nwg <= kDirect;
     // words of the sums, [group][word][member] with member wg / kLeaders of
@@ -382,7 +392,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 #pragma unroll
                 for (int q = 0; q < 2 * nv; ++q) ok &= (uint32_t)(w[q] >> 32) == epoch;
                 if (ok) break;
-                if (wall_clock64() > sh.deadline) {
+                if (late()) {
                     sh.dead = 1;
                     break;
                 }
@@ -436,7 +446,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
 #pragma unroll
                 for (int q = 0; q < NW; ++q) ok &= (uint32_t)(h[q] >> 32) == epoch;
                 if (ok) break;
-                if (wall_clock64() > sh.deadline) {
+                if (late()) {
                     sh.dead = 1;
                     break;
                 }
@@ -587,7 +597,7 @@ __global__ __launch_bounds__(kRBlock) void k_resident(ResidentArgs a)
     for (int s = t; s < tile_words; s += kRBlock) tile[s] = make_double2(0.0, 0.0);
     if (t == 0) {
         sh.dead = 0;
-        sh.deadline = started + a.wait_ticks;
+        sh.deadline = deadline;
     }
     __syncthreads();
     const double2 *in = EIG ? a.eig.u1 : a.state_in(0);
